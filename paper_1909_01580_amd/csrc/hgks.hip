@@ -245,11 +245,12 @@ GasParams<T> gas_params(const hgks_config& cfg) {
   GasParams<T> g;
   const double K = (5.0 - 3.0 * cfg.gamma) / (cfg.gamma - 1.0);
   g.gm1 = T(cfg.gamma - 1.0);
-  g.K = T(K);
-  g.K3 = T(K + 3.0);
   g.inv_K3 = T(1.0 / (K + 3.0));
   g.two_gm1 = T(2.0 / (cfg.gamma - 1.0));
-  g.K2 = T(K + 2.0);
+  g.K2h = T(0.5 * (K + 2.0));
+  g.K3h = T(0.5 * (K + 3.0));
+  g.K4h = T(0.5 * (K + 4.0));
+  g.K5 = T(K + 5.0);
   g.mu = T(cfg.mu);
   g.tau_eps = T(cfg.tau_eps);
   g.tau_C = T(cfg.tau_C);

@@ -51,7 +51,8 @@ int main() {
   // A Taylor-Green-like interface state: rho ~ 1, p ~ 71.4, |U| ~ 1.
   GasParams<Cnt> g;
   const double K = (5.0 - 3.0 * 1.4) / 0.4;
-  g.gm1 = Cnt(0.4); g.K = Cnt(K); g.K3 = Cnt(K + 3.0); g.K2 = Cnt(K + 2.0);
+  g.gm1 = Cnt(0.4); g.K2h = Cnt(0.5 * (K + 2.0)); g.K3h = Cnt(0.5 * (K + 3.0)); g.K4h = Cnt(0.5 * (K + 4.0));
+  g.K5 = Cnt(K + 5.0);
   g.inv_K3 = Cnt(1.0 / (K + 3.0)); g.two_gm1 = Cnt(2.0 / 0.4);
   g.mu = Cnt(1.0 / 1600.0); g.tau_eps = Cnt(0.01); g.tau_C = Cnt(1.0); g.viscous = 1;
 
