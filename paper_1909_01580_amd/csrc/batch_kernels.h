@@ -179,7 +179,13 @@ __global__ void __launch_bounds__(kBlock) HGKS_FLUX_OCCUPANCY
     const unsigned nb[3] = {b.nt_flux[0], b.nt_flux[1], b.nt_flux[2]};
     int D;
     flux_block(t - b.t_flux, nb, D, lt);
-    flux_box_face<TC, PR, FS, kStage>(cf, mk, face + b.face_off[D], b.G, b.gp, dtg, idtg, lt, D, stage);
+    TC* fd = face + b.face_off[D];
+    if (D == 0)
+      flux_box_face<0, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, stage);
+    else if (D == 1)
+      flux_box_face<1, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, stage);
+    else
+      flux_box_face<2, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, stage);
   });
 }
 

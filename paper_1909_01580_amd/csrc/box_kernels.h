@@ -600,17 +600,34 @@ HGKS_FN FaceAxes face_axes(int D) {
   return FaceAxes{D, D == 2 ? 0 : D + 1, D == 0 ? 2 : D - 1};
 }
 
-// Value and gradient of the five variables of reconstructed cell `cell` at
-// the point with local coordinates (xD, xA, xB) of the unit cube, in the
-// local frame of a face normal to axis D: W = (rho, M_D, M_A, M_B, E),
-// dW[j] = derivative along local axis j.  The stored quadratic (x, y, z,
-// xx, yy, zz, xy, yz, xz in global axes) is read with its coefficients
+// Value and unit-cube gradient of a quadratic about the cell mean q at a
+// Gauss point of the face on the high (S = +1) or low (S = -1) side of local
+// axis D, in local axes: c = (D, A, B, DD, AA, BB, DA, AB, DB) and (xa, xb)
+// the Gauss nodes along A and B.  xi_D^2 - 1/12 = 1/6 and xi_A^2 = xi_B^2 =
+// 1/12 there, so the AA and BB terms leave the value; 13 instructions where
+// the general quad_eval takes 24.
+template <int S, typename T>
+HGKS_FN void face_quad(T q, const T (&c)[9], T xa, T xb, T& val, T (&g)[3]) {
+  const T half = T(0.5 * S);
+  const T sa = c[1] + half * c[6];
+  const T sb = c[2] + half * c[8] + xa * c[7];
+  g[0] = c[0] + T(S) * c[3] + xa * c[6] + xb * c[8];
+  g[1] = sa + T(2) * xa * c[4] + xb * c[7];
+  g[2] = sb + T(2) * xb * c[5];
+  val = q + half * c[0] + T(1.0 / 6.0) * c[3] + xa * sa + xb * sb;
+}
+
+// Value and gradient of the five variables of a reconstructed cell at a
+// Gauss point (xa, xb) of its face on side S of axis D, in the local frame
+// of the face: W = (rho, M_D, M_A, M_B, E), dW[j] = derivative along local
+// axis j.  The stored quadratic (x, y, z, xx, yy, zz, xy, yz, xz in global
+// axes; rows 10 v + k, CB elements apart) is read with its coefficients
 // permuted to the local axes: local linear and square terms of axis j come
 // from global axis (D, A, B)[j], the local mixed terms (DA, AB, DB) from
 // the global mixed terms 6 + D, 6 + A, 6 + B.  D is a template parameter
 // so that every load has a constant offset from the cell's address.
-template <int D, int CB, typename TC>
-HGKS_FN void eval_rows_gp(const TC* cv, TC xD, TC xA, TC xB, bool fallback, const TC (&invd)[3], TC (&W)[5],
+template <int D, int S, int CB, typename TC>
+HGKS_FN void eval_rows_gp(const TC* cv, TC xa, TC xb, bool fallback, const TC (&invd)[3], TC (&W)[5],
                           TC (&dW)[3][5]) {
   constexpr int A = (D + 1) % 3, B = (D + 2) % 3;
   constexpr int lv[5] = {0, 1 + D, 1 + A, 1 + B, 4};
@@ -621,9 +638,8 @@ HGKS_FN void eval_rows_gp(const TC* cv, TC xD, TC xA, TC xB, bool fallback, cons
     TC c[9];
 #pragma unroll
     for (int m = 0; m < 9; ++m) c[m] = ck[(cp[m] + 1) * CB];
-    TC val, g[3];
-    quad_eval(ck[0], c, xD, xA, xB, val, g[0], g[1], g[2]);
-    W[kk] = val;
+    TC g[3];
+    face_quad<S>(ck[0], c, xa, xb, W[kk], g);
 #pragma unroll
     for (int j = 0; j < 3; ++j) dW[j][kk] = g[j] * invd[j];
   }
@@ -641,23 +657,11 @@ HGKS_FN void eval_rows_gp(const TC* cv, TC xD, TC xA, TC xB, bool fallback, cons
   }
 }
 
-// The 50 values of a cell are rows 10 v + k, CB elements apart.
-template <int D, typename TC>
-HGKS_FN void eval_box_gp(const TC* __restrict__ coef, size_t cell, TC xD, TC xA, TC xB, bool fallback,
-                         const TC (&invd)[3], TC (&W)[5], TC (&dW)[3][5]) {
-  eval_rows_gp<D, kCB<TC>>(coef + coef_cell<TC>(cell), xD, xA, xB, fallback, invd, W, dW);
-}
-
-// eval_box_gp for a direction D that is uniform over the workgroup.
-template <typename TC>
-HGKS_FN void eval_box_gp_dir(int D, const TC* __restrict__ coef, size_t cell, TC xD, TC xA, TC xB,
-                             bool fallback, const TC (&invd)[3], TC (&W)[5], TC (&dW)[3][5]) {
-  if (D == 0)
-    eval_box_gp<0>(coef, cell, xD, xA, xB, fallback, invd, W, dW);
-  else if (D == 1)
-    eval_box_gp<1>(coef, cell, xD, xA, xB, fallback, invd, W, dW);
-  else
-    eval_box_gp<2>(coef, cell, xD, xA, xB, fallback, invd, W, dW);
+// The 50 values of a cell of the coefficient array.
+template <int D, int S, typename TC>
+HGKS_FN void eval_box_gp(const TC* __restrict__ coef, size_t cell, TC xa, TC xb, bool fallback, const TC (&invd)[3],
+                         TC (&W)[5], TC (&dW)[3][5]) {
+  eval_rows_gp<D, S, kCB<TC>>(coef + coef_cell<TC>(cell), xa, xb, fallback, invd, W, dW);
 }
 
 // Value and gradient (local axes D, A, B; per unit length) at the Gauss
@@ -669,9 +673,9 @@ HGKS_FN void eval_box_gp_dir(int D, const TC* __restrict__ coef, size_t cell, TC
 // eigenvectors are formed (the fence keeps the loads there), so that their
 // latency overlaps it; from LDS each field's nine are read where they are
 // used, which keeps the registers of the other 36 free.
-template <int D, bool PRE = true, typename TC>
-__device__ __forceinline__ void eval_char_gp(const TC* cv, const double (&Qbar)[5], double gamma, TC xD, TC xA,
-                                             TC xB, bool fallback, const TC (&invd)[3], TC (&W)[5],
+template <int D, int S, bool PRE = true, typename TC>
+__device__ __forceinline__ void eval_char_gp(const TC* cv, const double (&Qbar)[5], double gamma, TC xa, TC xb,
+                                             bool fallback, const TC (&invd)[3], TC (&W)[5],
                                              TC (&dW)[3][5]) {
   constexpr int A = (D + 1) % 3, B = (D + 2) % 3, CB = kCB<TC>;
   constexpr int lv[5] = {0, 1 + D, 1 + A, 1 + B, 4};
@@ -699,7 +703,7 @@ __device__ __forceinline__ void eval_char_gp(const TC* cv, const double (&Qbar)[
 #pragma unroll
       for (int m = 0; m < 9; ++m) c[m] = PRE ? call[f][m] : cv[(f * 10 + cp[m] + 1) * CB];
       TC du, g[3];
-      quad_eval(TC(0), c, xD, xA, xB, du, g[0], g[1], g[2]);
+      face_quad<S>(TC(0), c, xa, xb, du, g);
       double r[5];
       char_rcol(Bs, f, r);
 #pragma unroll
@@ -717,18 +721,6 @@ __device__ __forceinline__ void eval_char_gp(const TC* cv, const double (&Qbar)[
 #pragma unroll
     for (int j = 0; j < 3; ++j) dW[j][kk] = grad[lv[kk]][j] * invd[j];
   }
-}
-
-template <bool PRE = true, typename TC>
-__device__ __forceinline__ void eval_char_gp_dir(int D, const TC* cv, const double (&Qbar)[5], double gamma, TC xD,
-                                                 TC xA, TC xB, bool fallback, const TC (&invd)[3], TC (&W)[5],
-                                                 TC (&dW)[3][5]) {
-  if (D == 0)
-    eval_char_gp<0, PRE>(cv, Qbar, gamma, xD, xA, xB, fallback, invd, W, dW);
-  else if (D == 1)
-    eval_char_gp<1, PRE>(cv, Qbar, gamma, xD, xA, xB, fallback, invd, W, dW);
-  else
-    eval_char_gp<2, PRE>(cv, Qbar, gamma, xD, xA, xB, fallback, invd, W, dW);
 }
 
 // LDS of the FP64 flux's right cells, in doubles: per group of 8 faces 50
@@ -757,10 +749,10 @@ __device__ __forceinline__ void copy_pieces(GlobalPtr src, LdsPtr dst) {
 // l / 4 (face_of_block).
 // PR: the extended viscous model (viscosity law, Prandtl correction); FS:
 // per-face coefficient arrays (characteristic reconstruction).
-template <typename TC, bool PR = false, bool FS = false, bool DMA = false>
+template <int D, typename TC, bool PR = false, bool FS = false, bool DMA = false>
 __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const uint32_t* __restrict__ mask,
                                               TC* __restrict__ face, const BoxGrid& G, const GasParams<TC>& gp,
-                                              TC dt, TC idt, unsigned lb, int D, TC* stage = nullptr) {
+                                              TC dt, TC idt, unsigned lb, TC* stage = nullptr) {
   const FaceAxes ax = face_axes(D);
   const int gpi = (int)(threadIdx.x & 3);
   int cR[3];
@@ -814,9 +806,9 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     {
       TC W[5], dW[3][5];
       if constexpr (FS)
-        eval_char_gp_dir(D, coefL + coef_cell<TC>(iL), Qbar, gp.gamma, TC(0.5), xa, xb, fbL, invd, W, dW);
+        eval_char_gp<D, +1>(coefL + coef_cell<TC>(iL), Qbar, gp.gamma, xa, xb, fbL, invd, W, dW);
       else
-        eval_box_gp_dir(D, coefL, iL, TC(0.5), xa, xb, fbL, invd, W, dW);
+        eval_box_gp<D, +1>(coefL, iL, xa, xb, fbL, invd, W, dW);
       // The copies are issued once the left cell's values have arrived: the
       // memory counter is waited on in issue order, so copies issued
       // earlier would hold up the left side's first use of its loads.
@@ -846,13 +838,9 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
       TC W[5], dW[3][5];
       const TC* cv = rs + (slot >> 3) * kStageGroup + (slot & 7u);
       if constexpr (FS)
-        eval_char_gp_dir<false>(D, cv, Qbar, gp.gamma, TC(-0.5), xa, xb, fbR, invd, W, dW);
-      else if (D == 0)
-        eval_rows_gp<0, 8>(cv, TC(-0.5), xa, xb, fbR, invd, W, dW);
-      else if (D == 1)
-        eval_rows_gp<1, 8>(cv, TC(-0.5), xa, xb, fbR, invd, W, dW);
+        eval_char_gp<D, -1, false>(cv, Qbar, gp.gamma, xa, xb, fbR, invd, W, dW);
       else
-        eval_rows_gp<2, 8>(cv, TC(-0.5), xa, xb, fbR, invd, W, dW);
+        eval_rows_gp<D, -1, 8>(cv, xa, xb, fbR, invd, W, dW);
       side_terms<-1, PR>(W, dW, gp, acc);
     }
   } else if constexpr (FS) {
@@ -865,20 +853,20 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     // while the flux accumulators are not yet live: there are registers for
     // each side's 45 coefficient loads to be in flight together.
     TC WL[5], dWL[3][5], WR[5], dWR[3][5];
-    eval_char_gp_dir(D, coefL + coef_cell<TC>(iL), Qbar, gp.gamma, TC(0.5), xa, xb, fbL, invd, WL, dWL);
-    eval_char_gp_dir(D, coefR + coef_cell<TC>(iR), Qbar, gp.gamma, TC(-0.5), xa, xb, fbR, invd, WR, dWR);
+    eval_char_gp<D, +1>(coefL + coef_cell<TC>(iL), Qbar, gp.gamma, xa, xb, fbL, invd, WL, dWL);
+    eval_char_gp<D, -1>(coefR + coef_cell<TC>(iR), Qbar, gp.gamma, xa, xb, fbR, invd, WR, dWR);
     side_terms<+1, PR, kAssignFirst<TC>>(WL, dWL, gp, acc);
     side_terms<-1, PR>(WR, dWR, gp, acc);
   } else {
     {
       TC W[5], dW[3][5];
-      eval_box_gp_dir(D, coefL, iL, TC(0.5), xa, xb, fbL, invd, W, dW);
+      eval_box_gp<D, +1>(coefL, iL, xa, xb, fbL, invd, W, dW);
       side_terms<+1, PR, kAssignFirst<TC>>(W, dW, gp, acc);
     }
     after_left_side(iR, acc);
     {
       TC W[5], dW[3][5];
-      eval_box_gp_dir(D, coefR, iR, TC(-0.5), xa, xb, fbR, invd, W, dW);
+      eval_box_gp<D, -1>(coefR, iR, xa, xb, fbR, invd, W, dW);
       side_terms<-1, PR>(W, dW, gp, acc);
     }
   }
@@ -937,13 +925,14 @@ __global__ void __launch_bounds__(kBlock) HGKS_FLUX_OCCUPANCY k_flux_box(
   int D;
   unsigned lb;
   flux_block(b, nb, D, lb);
-  TC* face = D == 0 ? fx : (D == 1 ? fy : fz);
-  if constexpr (sizeof(TC) == 8) {
-    __shared__ double stage[kBlock / 64 * kStageWave];
-    flux_box_face<TC, PR, FS, true>(coef, mask, face, G, gp, dt, idt, lb, D, stage);
-  } else {
-    flux_box_face<TC, PR, FS>(coef, mask, face, G, gp, dt, idt, lb, D);
-  }
+  constexpr bool kStage = sizeof(TC) == 8;
+  __shared__ TC stage[kStage ? kBlock / 64 * kStageWave : 1];
+  if (D == 0)
+    flux_box_face<0, TC, PR, FS, kStage>(coef, mask, fx, G, gp, dt, idt, lb, stage);
+  else if (D == 1)
+    flux_box_face<1, TC, PR, FS, kStage>(coef, mask, fy, G, gp, dt, idt, lb, stage);
+  else
+    flux_box_face<2, TC, PR, FS, kStage>(coef, mask, fz, G, gp, dt, idt, lb, stage);
 }
 
 // ---------------------------------------------------------------- update

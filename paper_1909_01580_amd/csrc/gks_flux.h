@@ -202,8 +202,9 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
   // half-line moments
   const T lam = T(0.5) * P.il;
   const T sl = d_sqrt(lam);
-  const T f0 = sg * T(0.56418958354775628694807945156077259) * sl * d_exp(-lam * uu);  // 1/sqrt(pi)
-  const T m0 = T(0.5) * d_erfc(-sg * sl * U);
+  const T ex = d_exp(-lam * uu);
+  const T f0 = sg * T(0.56418958354775628694807945156077259) * sl * ex;  // 1/sqrt(pi)
+  const T m0 = T(0.5) * d_erfc(-sg * sl * U, ex);
   const T hf = h * f0;
   const T m1 = U * m0 + hf;
   const T m2 = U * m1 + h * m0;
@@ -294,7 +295,7 @@ HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>
 // hides behind another's arithmetic.  Left to itself the compiler would
 // keep one FP64 wave per SIMD (over 256 registers); a third FP64 wave does
 // not fit without spilling the left side's sums.
-#define HGKS_FLUX_OCCUPANCY __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 ? 3 : 3)))
+#define HGKS_FLUX_OCCUPANCY __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 ? 2 : 3)))
 
 // Orders the loads of the right cell after the left side's terms.  The
 // address gets a dependence on the left side's last results through an

@@ -40,7 +40,7 @@ inline Cnt log(Cnt x) { ++cnt::tr; return Cnt(std::log(x.v)); }
 
 namespace hgks {
 template <> HGKS_FN Cnt d_exp<Cnt>(Cnt x) { ++cnt::tr; return Cnt(std::exp(x.v)); }
-template <> HGKS_FN Cnt d_erfc<Cnt>(Cnt x) { ++cnt::tr; return Cnt(std::erfc(x.v)); }
+template <> HGKS_FN Cnt d_erfc<Cnt>(Cnt x, Cnt) { ++cnt::tr; return Cnt(std::erfc(x.v)); }
 template <> HGKS_FN Cnt d_sqrt<Cnt>(Cnt x) { ++cnt::tr; return Cnt(std::sqrt(x.v)); }
 template <> HGKS_FN Cnt d_rcp<Cnt>(Cnt x) { ++cnt::dv; return Cnt(1.0 / x.v); }
 }  // namespace hgks
@@ -70,12 +70,12 @@ int main() {
   FluxAcc<Cnt> acc;
   {
     Cnt W[5], dW[3][5];
-    eval_box_gp<0>(coef, 0, Cnt(0.5), Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
+    eval_box_gp<0, +1>(coef, 0, Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
     side_terms<+1, false, true>(W, dW, g, acc);
   }
   {
     Cnt W[5], dW[3][5];
-    eval_box_gp<0>(coef, 1, Cnt(-0.5), Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
+    eval_box_gp<0, -1>(coef, 1, Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
     side_terms<-1>(W, dW, g, acc);
   }
   Cnt F[5], dF[5];
@@ -93,12 +93,12 @@ int main() {
     FluxAcc<Cnt> accp;
     {
       Cnt W[5], dW[3][5];
-      eval_box_gp<0>(coef, 0, Cnt(0.5), Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
+      eval_box_gp<0, +1>(coef, 0, Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
       side_terms<+1, true, true>(W, dW, g, accp);
     }
     {
       Cnt W[5], dW[3][5];
-      eval_box_gp<0>(coef, 1, Cnt(-0.5), Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
+      eval_box_gp<0, -1>(coef, 1, Cnt(0.2887), Cnt(-0.2887), false, invd, W, dW);
       side_terms<-1, true>(W, dW, g, accp);
     }
     finish_flux<true>(accp, g, Cnt(1.5e-3), Cnt(1.0 / 1.5e-3), F, dF);
