@@ -162,12 +162,13 @@ __global__ void __launch_bounds__(kBlock) k_batch_char_recon(const BatchGrid<TC>
 // tile's copies are issued.  FS: the per-face arrays of the
 // characteristic reconstruction.
 template <typename TC, bool LOOP, bool PR = false, bool FS = false>
-__global__ void __launch_bounds__(kBlock) HGKS_FLUX_OCCUPANCY
+__global__ void __launch_bounds__(kFluxLanes) HGKS_FLUX_OCCUPANCY
     k_batch_flux(const BatchGrid<TC>* __restrict__ B, int ng, unsigned ntiles, const TC* __restrict__ coef,
                  const uint32_t* __restrict__ mask, TC* __restrict__ face, const double* __restrict__ dt) {
   constexpr bool kStage = sizeof(TC) == 8;
-  __shared__ TC stage[kStage ? kBlock / 64 * kStageWave : 1];
-  for_tiles<LOOP>(ntiles, [&](unsigned t) {
+  __shared__ TC stage[kStage ? kFluxLanes / 64 * kStageWave : 1];
+  for_tiles<LOOP>(ntiles * kFluxSubs, [&](unsigned ts) {
+    const unsigned t = ts / kFluxSubs, sub = ts % kFluxSubs;
     const int g = batch_grid_of<TC, true>(B, ng, t);
     const BatchGrid<TC>& b = B[g];
     if (!(dt[g] > 0.0)) return;  // a grid without a time step is not advanced
@@ -181,11 +182,11 @@ __global__ void __launch_bounds__(kBlock) HGKS_FLUX_OCCUPANCY
     flux_block(t - b.t_flux, nb, D, lt);
     TC* fd = face + b.face_off[D];
     if (D == 0)
-      flux_box_face<0, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, stage);
+      flux_box_face<0, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, sub, stage);
     else if (D == 1)
-      flux_box_face<1, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, stage);
+      flux_box_face<1, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, sub, stage);
     else
-      flux_box_face<2, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, stage);
+      flux_box_face<2, TC, PR, FS, kStage>(cf, mk, fd, b.G, b.gp, dtg, idtg, lt, sub, stage);
   });
 }
 

@@ -727,7 +727,7 @@ __device__ __forceinline__ void eval_char_gp(const TC* cv, const double (&Qbar)[
 // rows of 8 and one row of padding (it moves the second group's reads to
 // other banks), two groups per wave.
 constexpr int kStageGroup = 50 * 8 + 8;
-constexpr int kStageWave = 2 * kStageGroup;
+constexpr int kStageWave = 2 * kStageGroup + 64 * kParked;
 
 typedef const void __attribute__((address_space(1)))* GlobalPtr;
 typedef void __attribute__((address_space(3)))* LdsPtr;
@@ -743,21 +743,27 @@ __device__ __forceinline__ void copy_pieces(GlobalPtr src, LdsPtr dst) {
   }
 }
 
+// Lanes of a flux workgroup.  No wave of the flux waits for another, so a
+// workgroup is as small as the hardware allows: a new one starts as soon as
+// one wave's registers and LDS are free.
+constexpr int kFluxLanes = 64;
+constexpr int kFluxSubs = 256 / kFluxLanes;  // workgroups per block of 64 faces
+
 // One lane = one Gauss point of one face normal to axis D; the four lanes of
-// a face sum their weighted fluxes with quad-permute moves.  Lane l of the
-// 256-lane block lb of direction D takes Gauss point l % 4 of face slot
-// l / 4 (face_of_block).
+// a face sum their weighted fluxes with quad-permute moves.  Lane l of part
+// `sub` of block lb of direction D takes Gauss point l % 4 of face slot
+// sub kFluxLanes / 4 + l / 4 (face_of_block).
 // PR: the extended viscous model (viscosity law, Prandtl correction); FS:
 // per-face coefficient arrays (characteristic reconstruction).
 template <int D, typename TC, bool PR = false, bool FS = false, bool DMA = false>
 __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const uint32_t* __restrict__ mask,
                                               TC* __restrict__ face, const BoxGrid& G, const GasParams<TC>& gp,
-                                              TC dt, TC idt, unsigned lb, TC* stage = nullptr) {
+                                              TC dt, TC idt, unsigned lb, unsigned sub, TC* stage = nullptr) {
   const FaceAxes ax = face_axes(D);
   const int gpi = (int)(threadIdx.x & 3);
   int cR[3];
   size_t f;
-  const bool live = face_of_block(G, D, lb, threadIdx.x >> 2, cR, f);
+  const bool live = face_of_block(G, D, lb, sub * (kFluxLanes / 4) + (threadIdx.x >> 2), cR, f);
   const int cL[3] = {cR[0] - (D == 0), cR[1] - (D == 1), cR[2] - (D == 2)};
   size_t iL = 0, iR = 0;
   {
@@ -776,7 +782,7 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
   const TC* coefL = FS ? coef + (size_t)(2 * D + 1) * G.fs_stride : coef;
   const TC* coefR = FS ? coef + (size_t)(2 * D) * G.fs_stride : coef;
   // the left side assigns the sums, the right side adds to them
-  FluxAcc<TC> acc;
+  FluxAcc<TC, DMA> acc;
   acc_begin(acc);
   if constexpr (DMA) {
     // The right cells' 50 values go to LDS by direct loads issued before
@@ -790,6 +796,7 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     static_assert(sizeof(TC) == 8 && kCB<TC> == 8, "rows of 8 doubles");
     const unsigned l = threadIdx.x & 63u;
     TC* rs = stage + (threadIdx.x >> 6) * kStageWave;
+    acc.slot = rs + 2 * kStageGroup + l;
     // in piece k of group g lane l copies row 4 k + l / 16 of face slot
     // 8 g + (l / 2) % 8, 32-bit half l % 2: byte 4 l of the piece
     unsigned cell0 = __shfl((unsigned)iR, (int)(((l >> 1) & 7u) * 4u));
@@ -870,6 +877,10 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
       side_terms<-1, PR>(W, dW, gp, acc);
     }
   }
+  if constexpr (DMA) {
+    pin_sums<PR>(acc);
+    asm volatile("" ::: "memory");
+  }
   TC F[5], dF[5];
   finish_flux<PR>(acc, gp, dt, idt, F, dF);
   // Face weight of Eq. (11): Gauss weight 1/4 times the area element.
@@ -916,23 +927,23 @@ HGKS_FN void flux_block(unsigned b, const unsigned (&nb)[3], int& D, unsigned& l
 
 // All faces of the three directions in one launch (see flux_block).
 template <typename TC, bool PR = false, bool FS = false>
-__global__ void __launch_bounds__(kBlock) HGKS_FLUX_OCCUPANCY k_flux_box(
+__global__ void __launch_bounds__(kFluxLanes) HGKS_FLUX_OCCUPANCY k_flux_box(
     const TC* __restrict__ coef, const uint32_t* __restrict__ mask, TC* __restrict__ fx, TC* __restrict__ fy,
     TC* __restrict__ fz, BoxGrid G, GasParams<TC> gp, TC dt, TC idt, unsigned nb0, unsigned nb1, unsigned nb2) {
-  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+  const unsigned p = xcd_block(blockIdx.x, gridDim.x), b = p / kFluxSubs, sub = p % kFluxSubs;
   if (b >= nb0 + nb1 + nb2) return;
   const unsigned nb[3] = {nb0, nb1, nb2};
   int D;
   unsigned lb;
   flux_block(b, nb, D, lb);
   constexpr bool kStage = sizeof(TC) == 8;
-  __shared__ TC stage[kStage ? kBlock / 64 * kStageWave : 1];
+  __shared__ TC stage[kStage ? kFluxLanes / 64 * kStageWave : 1];
   if (D == 0)
-    flux_box_face<0, TC, PR, FS, kStage>(coef, mask, fx, G, gp, dt, idt, lb, stage);
+    flux_box_face<0, TC, PR, FS, kStage>(coef, mask, fx, G, gp, dt, idt, lb, sub, stage);
   else if (D == 1)
-    flux_box_face<1, TC, PR, FS, kStage>(coef, mask, fy, G, gp, dt, idt, lb, stage);
+    flux_box_face<1, TC, PR, FS, kStage>(coef, mask, fy, G, gp, dt, idt, lb, sub, stage);
   else
-    flux_box_face<2, TC, PR, FS, kStage>(coef, mask, fz, G, gp, dt, idt, lb, stage);
+    flux_box_face<2, TC, PR, FS, kStage>(coef, mask, fz, G, gp, dt, idt, lb, sub, stage);
 }
 
 // ---------------------------------------------------------------- update

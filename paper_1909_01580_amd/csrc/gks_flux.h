@@ -79,10 +79,18 @@ struct GasParams {
 // Running sums over the two sides of the interface: the conservative
 // variables Q0 of g_0 and their derivatives, X4 = rho <u psi>, X5 = <u N
 // psi>, X6 = <u A psi>.  X4[0] is Q0[1] and is not kept.
-template <typename T>
+//
+// PARK: the first kParked entries of dQ0 live in LDS, entry k of a lane at
+// slot[64 k] (slot: the lane's own column of its wave's area, which no other
+// lane touches), so that they hold no registers while the right side is
+// formed.
+constexpr int kParked = 13;
+
+template <typename T, bool PARK = false>
 struct FluxAcc {
   T Q0[5];
   T dQ0[3][5];
+  T* slot = nullptr;
   T X4[5], X5[5], X6[5];
   T p[2];
   // Prandtl correction only: <N psi> and <A psi> over the half lines, which
@@ -99,8 +107,8 @@ struct FluxAcc {
 template <typename T>
 inline constexpr bool kAssignFirst = sizeof(T) == 8;
 
-template <typename T>
-HGKS_FN void acc_zero(FluxAcc<T>& A) {
+template <typename T, bool PARK>
+HGKS_FN void acc_zero(FluxAcc<T, PARK>& A) {
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
     A.Q0[i] = T(0); A.X4[i] = T(0); A.X5[i] = T(0); A.X6[i] = T(0);
@@ -111,8 +119,8 @@ HGKS_FN void acc_zero(FluxAcc<T>& A) {
 
 // Ready the sums for the first side of a face: zeroed unless that side
 // assigns them.
-template <typename T>
-HGKS_FN void acc_begin(FluxAcc<T>& A) {
+template <typename T, bool PARK>
+HGKS_FN void acc_begin(FluxAcc<T, PARK>& A) {
   if constexpr (!kAssignFirst<T>) acc_zero(A);
 }
 
@@ -123,6 +131,22 @@ HGKS_FN void put(T& y, T x) {
     y += x;
   else
     y = x;
+}
+
+// Entry i of A.dQ0[j] (+)= x, and its value.
+template <bool ACC, typename T, bool PARK>
+HGKS_FN void put_dq(FluxAcc<T, PARK>& A, int j, int i, T x) {
+  const int k = 5 * j + i;
+  if (PARK && k < kParked)
+    put<ACC>(A.slot[64 * k], x);
+  else
+    put<ACC>(A.dQ0[j][i], x);
+}
+
+template <typename T, bool PARK>
+HGKS_FN T get_dq(const FluxAcc<T, PARK>& A, int j, int i) {
+  const int k = 5 * j + i;
+  return PARK && k < kParked ? A.slot[64 * k] : A.dQ0[j][i];
 }
 
 // Primitive quantities of a state with conservative variables Q, from one
@@ -178,6 +202,15 @@ HGKS_FN void time_derivative(const Prim<T>& P, const PGrad<T> (&d)[3], T div, co
   a.th = -(g.gm1 * P.h * div + P.U * d[0].th + P.V * d[1].th + P.W * d[2].th);
 }
 
+// Keeps the compiler from moving instructions across this point (no
+// instruction of its own).
+template <bool ON>
+HGKS_FN void sched_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (ON) __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // Contributions of one side (sg = +1: left state, particles with u > 0;
 // sg = -1: right state, u < 0; sg may be a runtime value).  W: conservative
 // variables in the local frame; dW[j]: their derivatives along n_x, n_y,
@@ -185,8 +218,8 @@ HGKS_FN void time_derivative(const Prim<T>& P, const PGrad<T> (&d)[3], T div, co
 // pair, whose terms are assigned to the sums rather than added to zeroed
 // ones (the same values; an add to 0.0 cannot be dropped by the compiler,
 // whereas here no zeroing or add is issued).
-template <bool PR = false, bool FIRST = false, typename T>
-HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams<T>& g, T sg, FluxAcc<T>& A,
+template <bool PR = false, bool FIRST = false, typename T, bool PARK>
+HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams<T>& g, T sg, FluxAcc<T, PARK>& A,
                           T& pside) {
   constexpr bool ACC = !FIRST;
   Prim<T> P;
@@ -211,6 +244,7 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
   const T m3h = T(0.5) * U * m2 + h * m1;
   const T m0h = T(0.5) * m0, m2h = T(0.5) * m2, f0h = T(0.5) * f0;
 
+  sched_fence<PARK>();
   // rho <psi> and rho <u psi>
   {
     const T r0 = P.rho * m0, r1 = P.rho * m1;
@@ -226,6 +260,7 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
   }
   // <a psi> of a derivative a of the state: g_k = <u^k a>, s the tangential
   // and internal part of the energy moment
+  sched_fence<PARK>();
   const T k0 = U * f0h * P.il;
   auto g0_of = [&](const PGrad<T>& a) { return a.r * m0 + a.mx * f0 - a.th * k0; };
   auto g1_of = [&](const PGrad<T>& a) { return a.r * m1 + a.mx * m0 + a.th * f0h; };
@@ -234,11 +269,12 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     const T q0 = g0_of(d[j]);
-    put<ACC>(A.dQ0[j][0], q0);
-    put<ACC>(A.dQ0[j][1], g1_of(d[j]));
-    put<ACC>(A.dQ0[j][2], V * q0 + d[j].my * m0);
-    put<ACC>(A.dQ0[j][3], W * q0 + d[j].mz * m0);
-    put<ACC>(A.dQ0[j][4], g2h_of(d[j]) + et * q0 + s_of(d[j]) * m0);
+    put_dq<ACC>(A, j, 0, q0);
+    put_dq<ACC>(A, j, 1, g1_of(d[j]));
+    put_dq<ACC>(A, j, 2, V * q0 + d[j].my * m0);
+    put_dq<ACC>(A, j, 3, W * q0 + d[j].mz * m0);
+    put_dq<ACC>(A, j, 4, g2h_of(d[j]) + et * q0 + s_of(d[j]) * m0);
+    sched_fence<PARK>();
   }
   const T div = d[0].mx + d[1].my + d[2].mz;
   // <u A psi> (and <A psi>)
@@ -260,6 +296,7 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
       put<ACC>(A.S6[4], q2h + et * q0 + s * m0);
     }
   }
+  sched_fence<PARK>();
   // <u N psi> (and <N psi>)
   {
     const T D = d[0].mx - g.inv_K3 * div, Dh = D * h;
@@ -285,8 +322,8 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
   pside = P.p;
 }
 
-template <int SIDE, bool PR = false, bool FIRST = false, typename T>
-HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>& g, FluxAcc<T>& A) {
+template <int SIDE, bool PR = false, bool FIRST = false, typename T, bool PARK>
+HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>& g, FluxAcc<T, PARK>& A) {
   side_terms_s<PR, FIRST>(W, dW, g, T(SIDE), A, A.p[SIDE > 0 ? 0 : 1]);
 }
 
@@ -295,23 +332,44 @@ HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>
 // hides behind another's arithmetic.  Left to itself the compiler would
 // keep one FP64 wave per SIMD (over 256 registers); a third FP64 wave does
 // not fit without spilling the left side's sums.
-#define HGKS_FLUX_OCCUPANCY __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 ? 2 : 3)))
+#define HGKS_FLUX_OCCUPANCY __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && FS ? 2 : 3)))
 
 // Orders the loads of the right cell after the left side's terms.  The
 // address gets a dependence on the left side's last results through an
 // empty asm, so the compiler cannot hoist the right cell's coefficient
 // loads into the left side's work, where both sides' values would be live
 // at once.
-template <typename T>
-__device__ __forceinline__ void after_left_side(size_t& idx, const FluxAcc<T>& A) {
+template <typename T, bool PARK>
+__device__ __forceinline__ void after_left_side(size_t& idx, const FluxAcc<T, PARK>& A) {
   asm volatile("" : "+v"(idx) : "v"(A.X6[0]), "v"(A.X6[4]), "v"(A.Q0[4]), "v"(A.X4[4]));
+}
+
+// Forms every sum here: the compiler would otherwise sink the sums that only
+// the last part of finish_flux reads past the branches before it, and hold
+// their operands (about 50 more registers) instead.
+template <bool PR, typename T, bool PARK>
+__device__ __forceinline__ void pin_sums(FluxAcc<T, PARK>& A) {
+  auto pin = [](T& x) { asm volatile("" : "+v"(x)); };
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    pin(A.Q0[i]);
+    if (i > 0) pin(A.X4[i]);
+    pin(A.X5[i]);
+    pin(A.X6[i]);
+    if (PR && i != 1) {
+      pin(A.S5[i]);
+      pin(A.S6[i]);
+    }
+  }
+#pragma unroll
+  for (int k = kParked; k < 15; ++k) pin(A.dQ0[2][k - 10]);
 }
 
 // Collision time of Sec. 4 from the two sides' pressures and the state of
 // g_0.  PR: the extended viscous model -- the viscosity law and the Prandtl
 // correction (either may be trivial: mu_exp = 0, pr_fix = 0).
-template <bool PR, typename T>
-HGKS_FN T collision_time(const FluxAcc<T>& A, const Prim<T>& P, const GasParams<T>& g, T dt) {
+template <bool PR, typename T, bool PARK>
+HGKS_FN T collision_time(const FluxAcc<T, PARK>& A, const Prim<T>& P, const GasParams<T>& g, T dt) {
   const T jump = d_abs(A.p[0] - A.p[1]) * d_rcp(A.p[0] + A.p[1]) * dt;
   // mu / p_0 = mu (rho_0 / p_0) (1 / rho_0); mu = mu0 (T / T0)^omega with
   // T = p_0 / rho_0 when a viscosity law is set
@@ -324,8 +382,8 @@ HGKS_FN T collision_time(const FluxAcc<T>& A, const Prim<T>& P, const GasParams<
 
 // Equilibrium part, collision time and the time fit.  On return F and dF
 // hold the flux and its time derivative in the local frame.
-template <bool PR = false, typename T>
-HGKS_FN void finish_flux(const FluxAcc<T>& A, const GasParams<T>& g, T dt, T idt, T (&F)[5], T (&dF)[5]) {
+template <bool PR = false, typename T, bool PARK>
+HGKS_FN void finish_flux(const FluxAcc<T, PARK>& A, const GasParams<T>& g, T dt, T idt, T (&F)[5], T (&dF)[5]) {
   Prim<T> P;
   primitives(A.Q0, g, P);
   const T U = P.U, V = P.V, W = P.W, h = P.h;
@@ -351,7 +409,10 @@ HGKS_FN void finish_flux(const FluxAcc<T>& A, const GasParams<T>& g, T dt, T idt
   const T k2 = T(0.5) * (U * U + V * V + W * W);
   PGrad<T> d[3], a;
 #pragma unroll
-  for (int j = 0; j < 3; ++j) prim_grad(A.dQ0[j], P, k2, g, d[j]);
+  for (int j = 0; j < 3; ++j) {
+    const T b[5] = {get_dq(A, j, 0), get_dq(A, j, 1), get_dq(A, j, 2), get_dq(A, j, 3), get_dq(A, j, 4)};
+    prim_grad(b, P, k2, g, d[j]);
+  }
   const T div = d[0].mx + d[1].my + d[2].mz;
   time_derivative(P, d, div, g, a);
 

@@ -1282,7 +1282,7 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
     // comes from global memory as before.
     static_assert(sizeof(TC) == 8 && kCB<TC> == 8, "rows of 8 doubles");
     const unsigned l = threadIdx.x & 63u;
-    TC* rs = stage + (threadIdx.x >> 6) * kStageWave;
+    TC* rs = stage + (threadIdx.x >> 6) * 2 * kStageGroup;
     unsigned cell0 = __shfl((unsigned)iR, (int)(((l >> 1) & 7u) * 4u));
     unsigned cell1 = __shfl((unsigned)iR, (int)((8u + ((l >> 1) & 7u)) * 4u));
     {
@@ -1421,7 +1421,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
   double* vface = D == 0 ? vx : (D == 1 ? vy : vz);
   __shared__ double stash[kHexStash<FS>][kBlock];
   if constexpr (sizeof(TC) == 8 && !FS) {
-    __shared__ double stage[kBlock / 64 * kStageWave];
+    __shared__ double stage[kBlock / 64 * 2 * kStageGroup];
     flux_hex_face<TC, PR, FS>(H, coef, geo, mask, face, vface, gp, dt, idt, N, lb, D, stash, stage);
   } else {
     flux_hex_face<TC, PR, FS>(H, coef, geo, mask, face, vface, gp, dt, idt, N, lb, D, stash);

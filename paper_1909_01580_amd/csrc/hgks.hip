@@ -321,13 +321,13 @@ hgks_status box_stage(hgks_ctx c, const double* qin, double dt) {
   unsigned nb[3];
   flux_block_counts(c->G, nb);
   prof_mark(c, HGKS_PHASE_FLUX, true);
-  const dim3 grid(pad8(nb[0] + nb[1] + nb[2]));
+  const dim3 grid(pad8((nb[0] + nb[1] + nb[2]) * kFluxSubs));
   const TC* fc = face_coef<TC>(c);
   TC* f[3] = {(TC*)c->face(0), (TC*)c->face(1), (TC*)c->face(2)};
   // compile-time variants: the extended viscous model and per-face arrays
   const bool ext = c->cfg.prandtl != 1.0 || c->cfg.mu_exponent != 0.0, fs = c->cfg.characteristic != 0;
 #define HGKS_FLUX_LAUNCH(E, F)                                                                                   \
-  hipLaunchKernelGGL((k_flux_box<TC, E, F>), grid, dim3(kBlock), 0, c->stream, fc, c->mask(), f[0], f[1], f[2], \
+  hipLaunchKernelGGL((k_flux_box<TC, E, F>), grid, dim3(kFluxLanes), 0, c->stream, fc, c->mask(), f[0], f[1], f[2], \
                      c->G, gp, TC(dt), TC(1.0 / dt), nb[0], nb[1], nb[2])
   if (ext && fs)
     HGKS_FLUX_LAUNCH(true, true);
@@ -1213,14 +1213,14 @@ hgks_status batch_stage(hgks_batch b, const double* qin, const double* dt_dev) {
   }
   {
     const bool loop = batch_loop(b, HGKS_PHASE_FLUX);
-    const dim3 grid(batch_wg(b, HGKS_PHASE_FLUX, b->tiles_flux));
+    const dim3 grid(batch_wg(b, HGKS_PHASE_FLUX, b->tiles_flux) * kFluxSubs);
     // characteristic variables: one workgroup per tile only (the per-face
     // instantiations are not built in the persistent form)
     auto flux = b->chr ? (b->ext ? k_batch_flux<TC, false, true, true> : k_batch_flux<TC, false, false, true>)
                 : loop ? (b->ext ? k_batch_flux<TC, true, true> : k_batch_flux<TC, true, false>)
                        : (b->ext ? k_batch_flux<TC, false, true> : k_batch_flux<TC, false, false>);
-    const dim3 fgrid = b->chr ? dim3(pad8(b->tiles_flux)) : grid;
-    hipLaunchKernelGGL(flux, fgrid, dim3(kBlock), 0, b->stream, D, b->ng, b->tiles_flux, (const TC*)coef,
+    const dim3 fgrid = b->chr ? dim3(pad8(b->tiles_flux) * kFluxSubs) : grid;
+    hipLaunchKernelGGL(flux, fgrid, dim3(kFluxLanes), 0, b->stream, D, b->ng, b->tiles_flux, (const TC*)coef,
                        (const uint32_t*)mask, (TC*)(b->ws + b->face), dt_dev);
   }
   return bcheck(b, hipGetLastError(), "batch stage");
