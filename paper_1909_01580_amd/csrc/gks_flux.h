@@ -327,11 +327,15 @@ HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>
   side_terms_s<PR, FIRST>(W, dW, g, T(SIDE), A, A.p[SIDE > 0 ? 0 : 1]);
 }
 
-// Register budget of the flux kernels: at least two waves per SIMD in FP64
-// (three in FP32), so that one wave's memory and transcendental latency
-// hides behind another's arithmetic.  Left to itself the compiler would
-// keep one FP64 wave per SIMD (over 256 registers); a third FP64 wave does
-// not fit without spilling the left side's sums.
+// Register budget of the flux kernels: three waves per SIMD (168 registers
+// in FP64).  The kernel is bound by its vector instruction count, and at
+// two waves a SIMD issues on 75% of its cycles, at three on 94%: 128^3
+// Taylor-Green FP64 launch 1.54 -> 1.39 ms (-> 1.34 with one-wave
+// workgroups).  Three FP64 waves fit without spills because part of the
+// sums is parked in LDS (kParked) and the sums are formed before
+// finish_flux (pin_sums).  The per-face form (FS) holds the eigenvectors
+// besides and keeps two waves: three spill 20 registers and lengthen the
+// 100^3 characteristic step from 4.71 to 5.00 ms.  FP32 fits four.
 #define HGKS_FLUX_OCCUPANCY __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && FS ? 2 : 3)))
 
 // Orders the loads of the right cell after the left side's terms.  The
