@@ -59,6 +59,22 @@ HGKS_FN T lin_bound(T bx, T by, T bz) {
   return T(0.5) * (d_abs(bx) + d_abs(by) + d_abs(bz));
 }
 
+// 1/x and 1/y of positive numbers.  In double one reciprocal of the product
+// serves both (11 issue slots instead of 16: the FP64 estimate takes four);
+// the product of two indicators stays far from the ends of its range.  In
+// float it might not, and the estimate costs less: two reciprocals.
+template <typename T>
+HGKS_FN void rcp_pair(T x, T y, T& ix, T& iy) {
+  if constexpr (sizeof(T) == 8) {
+    const T r = d_rcp(x * y);
+    ix = r * y;
+    iy = r * x;
+  } else {
+    ix = d_rcp(x);
+    iy = d_rcp(y);
+  }
+}
+
 // Least-squares quadratic of the big stencil (closed form above).
 template <typename T>
 HGKS_FN void big_quadratic(const T (&d)[27], T (&a)[9]) {
@@ -128,40 +144,61 @@ HGKS_FN void weno_box(const T (&d)[27], const WenoParams<T>& P, BoxRecon<T>& out
   // and the combined linear part sum_m (omega_m - Gamma omega_0 / gamma_0)
   // b^m / S is (Gamma tau / S) sum_m (r_m - r_0) b^m.  The pass gathers
   // sum |beta_0 - beta_m| (tau), sum r_m and sum (r_m - r_0) b^m; tau enters
-  // afterwards, and no sub-stencil's indicator is kept.  Sub-stencils in the
-  // order of the printed S_1..S_8 and their two cyclic permutations: triple
-  // t, then s_c, s_b, s_a in (+, -).
+  // afterwards, and no sub-stencil's indicator is kept.
+  //
+  // Sub-stencils of one axis triple (a, b; c) share: four signed pairs
+  // (s_a, s_b) give four slopes along a and b, two signs s_c two slopes
+  // along c, and the eight sub-stencils are their combinations.  So the
+  // slopes along a and b (carried times 3) are weighted with the sum of
+  // the r_m over s_c, those along c with the sum over the pairs, and the
+  // bound is the largest pair bound plus the largest |b_c|.
   const T r0 = d_rcp(beta0 + P.eps);
-  T tsum = T(0), rsum = T(0), db[3] = {T(0), T(0), T(0)};
+  T tsum = T(0), rsum = T(0), db[3] = {T(0), T(0), T(0)}, db3[3] = {T(0), T(0), T(0)};
   T bnd = T(0.5) * (d_abs(a[0]) + d_abs(a[1]) + d_abs(a[2])) +
           T(1.0 / 6.0) * (d_abs(a[3]) + d_abs(a[4]) + d_abs(a[5])) +
           T(0.14433756729740644113) * (d_abs(a[6]) + d_abs(a[7]) + d_abs(a[8]));
+  const T r0_2 = T(2) * r0, r0_4 = T(4) * r0;
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     const int ea = t, eb = (t + 1) % 3, ec = (t + 2) % 3;
+    const T ka = T(1.0 / 9.0) * P.kl[ea], kb = T(1.0 / 9.0) * P.kl[eb];
+    // slopes along c and their part of the indicator (with eps)
+    int oc[3] = {0, 0, 0};
+    oc[ec] = 1;
+    const T cp = d[sidx3(oc)];
+    oc[ec] = -1;
+    const T cm = -d[sidx3(oc)];
+    const T ecp = P.kl[ec] * cp * cp, ecm = P.kl[ec] * cm * cm;
+    T ab[4], bb3[4], q[4], babs = T(0);
 #pragma unroll
-    for (int ic = 0; ic < 2; ++ic)
+    for (int p = 0; p < 4; ++p) {
+      const int sa = (p & 1) ? -1 : 1, sb = (p & 2) ? -1 : 1;
+      int oa[3] = {0, 0, 0}, ob[3] = {0, 0, 0}, oab[3] = {0, 0, 0};
+      oa[ea] = sa; ob[eb] = sb; oab[ea] = sa; oab[eb] = sb;
+      const T da = d[sidx3(oa)], db_ = d[sidx3(ob)], dab = d[sidx3(oab)];
+      ab[p] = T(2) * da - db_ + dab;   // 3 s_a b_a
+      bb3[p] = T(2) * db_ - da + dab;  // 3 s_b b_b
+      q[p] = ka * ab[p] * ab[p] + kb * bb3[p] * bb3[p];
+      babs = d_max(babs, d_abs(ab[p]) + d_abs(bb3[p]));
+    }
+    T rp = T(0), rm = T(0);
 #pragma unroll
-      for (int ib = 0; ib < 2; ++ib)
-#pragma unroll
-        for (int ia = 0; ia < 2; ++ia) {
-          const int sa = ia ? -1 : 1, sb = ib ? -1 : 1, sc = ic ? -1 : 1;
-          int oa[3] = {0, 0, 0}, ob[3] = {0, 0, 0}, oab[3] = {0, 0, 0}, oc[3] = {0, 0, 0};
-          oa[ea] = sa; ob[eb] = sb; oab[ea] = sa; oab[eb] = sb; oc[ec] = sc;
-          const T da = d[sidx3(oa)], db_ = d[sidx3(ob)], dab = d[sidx3(oab)], dc = d[sidx3(oc)];
-          const T bc = T(sc) * dc;
-          const T ba = T(sa) * (T(2) * da - db_ + dab) * T(1.0 / 3.0);
-          const T bb = T(sb) * (T(2) * db_ - da + dab) * T(1.0 / 3.0);
-          const T beta = P.kl[ea] * ba * ba + P.kl[eb] * bb * bb + P.kl[ec] * bc * bc;
-          tsum += d_abs(beta0 - beta);
-          const T rm = d_rcp(beta + P.eps);
-          rsum += rm;
-          const T dr = rm - r0;
-          db[ea] += dr * ba;
-          db[eb] += dr * bb;
-          db[ec] += dr * bc;
-          bnd = d_max(bnd, T(0.5) * (d_abs(ba) + d_abs(bb) + d_abs(bc)));
-        }
+    for (int p = 0; p < 4; ++p) {
+      const T sa = (p & 1) ? T(-1) : T(1), sb = (p & 2) ? T(-1) : T(1);
+      const T b0 = q[p] + ecp, b1 = q[p] + ecm;
+      tsum += d_abs(beta0 - b0);
+      tsum += d_abs(beta0 - b1);
+      T r[2];
+      rcp_pair(b0 + P.eps, b1 + P.eps, r[0], r[1]);
+      rp += r[0];
+      rm += r[1];
+      const T ds = (r[0] + r[1]) - r0_2;
+      db3[ea] += ds * (sa * ab[p]);
+      db3[eb] += ds * (sb * bb3[p]);
+    }
+    rsum += rp + rm;
+    db[ec] += (rp - r0_4) * cp + (rm - r0_4) * cm;
+    bnd = d_max(bnd, T(1.0 / 6.0) * babs + T(0.5) * d_max(d_abs(cp), d_abs(cm)));
   }
   const T tau = tsum * T(1.0 / 24.0);
   const T w0r = T(1) + tau * r0;  // omega_0 / gamma_0
@@ -169,7 +206,7 @@ HGKS_FN void weno_box(const T (&d)[27], const WenoParams<T>& P, BoxRecon<T>& out
   const T w0g = w0r * iS;           // wbar_0 / gamma_0
   const T gl = P.Gamma * tau * iS;  // weight of sum (r_m - r_0) b^m
 #pragma unroll
-  for (int e = 0; e < 3; ++e) out.c[e] = w0g * a[e] + gl * db[e];
+  for (int e = 0; e < 3; ++e) out.c[e] = w0g * a[e] + gl * (db[e] + T(1.0 / 3.0) * db3[e]);
 #pragma unroll
   for (int k = 3; k < 9; ++k) out.c[k] = w0g * a[k];
   out.bound = bnd;
