@@ -46,6 +46,8 @@ struct BoxGrid {
   // rows along y; reciprocals of n0 band n2, n0 band and n0 (tail height).
   int band, band_full, band_tail;
   double inv_band[3];
+  // Integer reciprocals of n0, n1; n0 band n2, n0 band, n0 (tail height).
+  struct { uint32_t m, s; } mag_n[2], mag_band[3];
   // Elements between the six per-face coefficient arrays of a cell
   // (reconstruction in characteristic variables: array 2 d + s holds the
   // quadratic for the cell's face normal to d on side s); 0 when one
@@ -66,6 +68,21 @@ HGKS_FN void split_index(uint32_t k, int e0, int e1, double i0, double i1, int& 
   c2 = (int)q1;
 }
 
+// k / d for k < 2^29 by a multiplication (scalar instructions where k is
+// uniform): m = ceil(2^(32+s) / d) with 2^s < d <= 2^(s+1), so m < 2^32 and
+// m d - 2^(32+s) < d, which times k stays below 2^(32+s).  d >= 2.
+template <typename M>
+inline void set_magic(M& g, uint32_t d) {
+  uint32_t s = 0;
+  while ((2ull << s) < d) ++s;
+  g.s = s;
+  g.m = (uint32_t)(((1ull << (32 + s)) + d - 1) / d);
+}
+template <typename M>
+HGKS_FN uint32_t div_magic(uint32_t k, const M& g) {
+  return (uint32_t)(((uint64_t)k * g.m) >> 32) >> g.s;
+}
+
 // Rows per band of the flux block order: the z-neighbour row of a cell is
 // band * n0 cells earlier in that order, close enough to be found in L2.
 constexpr int kFluxBand = 16;
@@ -84,6 +101,10 @@ inline void set_index_split(BoxGrid& G, int band = kFluxBand) {
   G.inv_band[0] = div_inv(G.n[0] * G.band * G.n[2]);
   G.inv_band[1] = div_inv(G.n[0] * G.band);
   G.inv_band[2] = div_inv(G.n[0] * (G.band_tail > 0 ? G.band_tail : 1));
+  for (int a = 0; a < 2; ++a) set_magic(G.mag_n[a], (uint32_t)G.n[a]);
+  set_magic(G.mag_band[0], (uint32_t)G.n[0] * G.band * G.n[2]);
+  set_magic(G.mag_band[1], (uint32_t)G.n[0] * G.band);
+  set_magic(G.mag_band[2], (uint32_t)G.n[0] * (G.band_tail > 0 ? G.band_tail : 1));
 }
 
 // Flux blocks of 64 faces per direction d: one per 64 cells (the faces on
@@ -182,6 +203,10 @@ template <typename TC>
 HGKS_FN size_t coef_cell(size_t cell) {
   return (cell / kCB<TC>) * 50 * kCB<TC> + cell % kCB<TC>;
 }
+template <typename TC>
+HGKS_FN size_t coef_cell(unsigned cell) {
+  return (size_t)(cell / kCB<TC>) * (50u * kCB<TC>) + cell % kCB<TC>;
+}
 
 // Elements of the coefficient array of NR reconstructed cells.
 constexpr size_t coef_elems(size_t NR, size_t elem_bytes) {
@@ -219,6 +244,117 @@ __device__ __forceinline__ int rec_index(const BoxGrid& G, int ax, int i) {
   const int n = G.n[ax];
   if (G.per[ax]) return i < 0 ? i + n : (i >= n ? i - n : i);
   return i + 1;
+}
+
+// Face of one lane: the cell c on its upper side, its left and right cells
+// in the reconstruction box, its index in the face grid.
+struct FaceLane {
+  int c[3];
+  unsigned iL, iR, f;
+  bool live;
+};
+
+// face_of_block for slot `first` + `lane` (lane < kFluxRow), `first` and lb
+// uniform over the wave.  Consecutive slots run along x (along the first
+// of the two other axes on an upper boundary plane), so where a row is at
+// least kFluxRow long the wave's faces lie in two rows at most: both rows'
+// coordinates and offsets are scalar arithmetic and a lane only picks its
+// row (some 15 vector instructions, where the per-lane split with 64-bit
+// index products took about 100).  Shorter rows take face_of_block.
+constexpr int kFluxRow = 16;
+
+template <int D>
+HGKS_FN FaceLane wave_face(const BoxGrid& G, unsigned lb, unsigned first, unsigned lane) {
+  FaceLane L;
+  const unsigned s1 = (unsigned)G.nr[0], s2 = (unsigned)G.nr[0] * (unsigned)G.nr[1];
+  const unsigned f1 = (unsigned)G.nf[D][0], f2 = f1 * (unsigned)G.nf[D][1];
+  const unsigned sD = D == 0 ? 1u : (D == 1 ? s1 : s2);
+  const unsigned ghost = (unsigned)G.g[0] + (unsigned)G.g[1] * s1 + (unsigned)G.g[2] * s2;
+  const unsigned N = (unsigned)G.n[0] * G.n[1] * G.n[2];
+  const unsigned nmain = (N + 63u) / 64u;
+  const bool bnd = lb >= nmain;
+  // axes of a boundary plane: a0 along the rows, a1 across them
+  constexpr int a0 = D == 0 ? 1 : 0, a1 = D == 2 ? 1 : 2;
+  const int row = bnd ? G.n[a0] : G.n[0];
+  if (row < kFluxRow) {
+    size_t f;
+    L.live = face_of_block(G, D, lb, first + lane, L.c, f);
+    L.f = (unsigned)f;
+    L.iR = (unsigned)L.c[0] + (unsigned)L.c[1] * s1 + (unsigned)L.c[2] * s2 + ghost;
+    L.iL = G.per[D] && L.c[D] == 0 ? L.iR + (unsigned)(G.n[D] - 1) * sD : L.iR - sD;
+    return L;
+  }
+  unsigned total, p, x, jA, kA, jB, kB;
+  if (!bnd) {
+    total = N;
+    const unsigned at = lb * 64u + first;
+    p = at < N ? at : N - 1;
+    const unsigned full = (unsigned)G.n[0] * G.band * G.band_full * G.n[2];
+    const bool in = p < full;
+    const unsigned b = in ? div_magic(p, G.mag_band[0]) : (unsigned)G.band_full;
+    const unsigned r = p - b * (unsigned)(G.n[0] * G.band * G.n[2]);
+    const unsigned hb = in ? (unsigned)G.band : (unsigned)G.band_tail;
+    const unsigned k = in ? div_magic(r, G.mag_band[1]) : div_magic(r, G.mag_band[2]);
+    const unsigned r2 = r - k * ((unsigned)G.n[0] * hb);
+    const unsigned j = div_magic(r2, G.mag_n[0]);
+    x = r2 - j * (unsigned)G.n[0];
+    jA = b * (unsigned)G.band + j;
+    kA = k;
+    // the next row: within the band, on the next plane, or of the next band
+    // (the last row of all repeats itself: no live lane passes it)
+    jB = jA + 1;
+    kB = k;
+    if (j + 1 == hb) {
+      jB = b * (unsigned)G.band;
+      kB = k + 1;
+      if (kB == (unsigned)G.n[2]) {
+        const bool last = jA + 1 == (unsigned)G.n[1];
+        jB = last ? jA : jA + 1;
+        kB = last ? kA : 0u;
+      }
+    }
+  } else {
+    total = (unsigned)G.n[a0] * (unsigned)G.n[a1];
+    const unsigned at = (lb - nmain) * 64u + first;
+    p = at < total ? at : total - 1;
+    jA = kA = div_magic(p, G.mag_n[a0]);
+    x = p - kA * (unsigned)G.n[a0];
+    jB = kB = kA + 1 < (unsigned)G.n[a1] ? kA + 1 : kA;
+  }
+  const unsigned xl = x + lane;
+  const bool carry = xl >= (unsigned)row;
+  const unsigned xf = carry ? xl - (unsigned)row : xl;
+  L.live = (bnd ? (lb - nmain) * 64u : lb * 64u) + first + lane < total;
+  if (!bnd) {
+    const unsigned rA = jA * s1 + kA * s2 + ghost, rB = jB * s1 + kB * s2 + ghost;
+    const unsigned fA = jA * f1 + kA * f2, fB = jB * f1 + kB * f2;
+    L.c[0] = (int)xf;
+    L.c[1] = (int)(carry ? jB : jA);
+    L.c[2] = (int)(carry ? kB : kA);
+    L.iR = xf + (carry ? rB : rA);
+    L.f = xf + (carry ? fB : fA);
+    const unsigned down = 0u - sD, wrap = (unsigned)(G.n[D] - 1) * sD;
+    if (D == 0) {
+      L.iL = L.iR + (G.per[0] && xf == 0 ? wrap : down);
+    } else {
+      const unsigned cA = D == 1 ? jA : kA, cB = D == 1 ? jB : kB;
+      const unsigned oA = G.per[D] && cA == 0 ? wrap : down, oB = G.per[D] && cB == 0 ? wrap : down;
+      L.iL = L.iR + (carry ? oB : oA);
+    }
+  } else {
+    const unsigned t0 = a0 == 0 ? 1u : s1, t1 = a1 == 1 ? s1 : s2;
+    const unsigned g0 = a0 == 0 ? 1u : f1, g1 = a1 == 1 ? f1 : f2, gD = D == 0 ? 1u : (D == 1 ? f1 : f2);
+    const unsigned top = (unsigned)G.n[D];
+    const unsigned rA = kA * t1 + top * sD + ghost, rB = kB * t1 + top * sD + ghost;
+    const unsigned fA = kA * g1 + top * gD, fB = kB * g1 + top * gD;
+    L.c[D] = (int)top;
+    L.c[a0] = (int)xf;
+    L.c[a1] = (int)(carry ? kB : kA);
+    L.iR = xf * t0 + (carry ? rB : rA);
+    L.f = xf * g0 + (carry ? fB : fA);
+    L.iL = L.iR - sD;
+  }
+  return L;
 }
 
 // ---------------------------------------------------------------- recon
@@ -659,7 +795,7 @@ HGKS_FN void eval_rows_gp(const TC* cv, TC xa, TC xb, bool fallback, const TC (&
 
 // The 50 values of a cell of the coefficient array.
 template <int D, int S, typename TC>
-HGKS_FN void eval_box_gp(const TC* __restrict__ coef, size_t cell, TC xa, TC xb, bool fallback, const TC (&invd)[3],
+HGKS_FN void eval_box_gp(const TC* __restrict__ coef, unsigned cell, TC xa, TC xb, bool fallback, const TC (&invd)[3],
                          TC (&W)[5], TC (&dW)[3][5]) {
   eval_rows_gp<D, S, kCB<TC>>(coef + coef_cell<TC>(cell), xa, xb, fallback, invd, W, dW);
 }
@@ -761,21 +897,15 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
                                               TC dt, TC idt, unsigned lb, unsigned sub, TC* stage = nullptr) {
   const FaceAxes ax = face_axes(D);
   const int gpi = (int)(threadIdx.x & 3);
-  int cR[3];
-  size_t f;
-  const bool live = face_of_block(G, D, lb, sub * (kFluxLanes / 4) + (threadIdx.x >> 2), cR, f);
-  const int cL[3] = {cR[0] - (D == 0), cR[1] - (D == 1), cR[2] - (D == 2)};
-  size_t iL = 0, iR = 0;
-  {
-    const size_t s1 = G.nr[0], s2 = (size_t)G.nr[0] * G.nr[1];
-    iL = rec_index(G, 2, cL[2]) * s2 + rec_index(G, 1, cL[1]) * s1 + rec_index(G, 0, cL[0]);
-    iR = rec_index(G, 2, cR[2]) * s2 + rec_index(G, 1, cR[1]) * s1 + rec_index(G, 0, cR[0]);
-  }
+  const FaceLane fl = wave_face<D>(G, lb, sub * (kFluxLanes / 4), threadIdx.x >> 2);
+  const unsigned iL = fl.iL;
+  unsigned iR = fl.iR;
   const TC xa = (gpi >> 1) ? TC(kGaussNode) : TC(-kGaussNode);
   const TC xb = (gpi & 1) ? TC(kGaussNode) : TC(-kGaussNode);
   const TC invd[3] = {TC(G.inv_dx[ax.D]), TC(G.inv_dx[ax.A]), TC(G.inv_dx[ax.B])};
-  const bool fbL = (mask[iL] >> (4 * (2 * D + 1) + gpi)) & 1u;
-  const bool fbR = (mask[iR] >> (4 * (2 * D) + gpi)) & 1u;
+  auto mask_of = [&](unsigned i) { return *(const uint32_t*)((const char*)mask + i * 4u); };
+  const bool fbL = (mask_of(iL) >> (4 * (2 * D + 1) + gpi)) & 1u;
+  const bool fbR = (mask_of(iR) >> (4 * (2 * D) + gpi)) & 1u;
 
   // the left cell's quadratic for its high face, the right cell's for its
   // low face (the same array unless the faces have their own)
@@ -799,8 +929,8 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     acc.slot = rs + 2 * kStageGroup + l;
     // in piece k of group g lane l copies row 4 k + l / 16 of face slot
     // 8 g + (l / 2) % 8, 32-bit half l % 2: byte 4 l of the piece
-    unsigned cell0 = __shfl((unsigned)iR, (int)(((l >> 1) & 7u) * 4u));
-    unsigned cell1 = __shfl((unsigned)iR, (int)((8u + ((l >> 1) & 7u)) * 4u));
+    unsigned cell0 = __shfl(iR, (int)(((l >> 1) & 7u) * 4u));
+    unsigned cell1 = __shfl(iR, (int)((8u + ((l >> 1) & 7u)) * 4u));
     // characteristic reconstruction: the face's mean state from the two
     // cells' conservative means gives R for both sides
     double Qbar[5];
@@ -837,7 +967,7 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     }
     // the right side's LDS reads wait for the left side's results and for
     // this wave's copies
-    size_t slot = threadIdx.x >> 2 & 15u;
+    unsigned slot = threadIdx.x >> 2 & 15u;
     after_left_side(slot, acc);
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("" ::: "memory");
@@ -892,13 +1022,15 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     F[i] = quad_xor_add<2>(quad_xor_add<1>(F[i]));
     dF[i] = quad_xor_add<2>(quad_xor_add<1>(dF[i]));
   }
-  if (live && gpi == 0) {
+  if (fl.live && gpi == 0) {
+    // 32-bit byte offset from each row's uniform base
     const size_t NF = (size_t)G.nf[D][0] * G.nf[D][1] * G.nf[D][2];
-    const int gv[5] = {0, 1 + ax.D, 1 + ax.A, 1 + ax.B, 4};
+    const unsigned fo = fl.f * (unsigned)sizeof(TC);
+    constexpr int gv[5] = {0, 1 + D, 1 + (D + 1) % 3, 1 + (D + 2) % 3, 4};
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
-      face[(size_t)gv[i] * NF + f] = F[i];
-      face[(size_t)(5 + gv[i]) * NF + f] = dF[i];
+      *(TC*)((char*)(face + (size_t)gv[i] * NF) + fo) = F[i];
+      *(TC*)((char*)(face + (size_t)(5 + gv[i]) * NF) + fo) = dF[i];
     }
   }
 }

@@ -30,23 +30,25 @@ template <> HGKS_FN double kconst<double>(double c) { return sreg(c); }
 
 // exp(x) in double: Cody and Waite's reduction x = k ln2 + r, k = rint(x /
 // ln2), |r| <= ln2 / 2, with ln2 split as hi + lo (hi has 21 significant
-// bits, so k hi is exact for every k that does not overflow), then the
-// Taylor polynomial of e^r to degree 13 (the first omitted term is below
-// 7e-18 relative) by Horner's rule, scaled by 2^k.  Arguments below -1000
-// are raised to -1000 (the result is 0 either way); NaN passes through.
-constexpr double exp_taylor_coef(int n) {
-  double f = 1.0;
-  for (int k = 2; k <= n; ++k) f /= k;
-  return f;
-}
+// bits, so k hi is exact for every k that does not overflow), then 1 + r +
+// r^2 q(r) by Horner's rule, q interpolating (e^r - 1 - r) / r^2 at the ten
+// Chebyshev nodes of that interval (computed in 60 digits; 1.6e-17
+// relative, two steps shorter than the Taylor polynomial), scaled by 2^k.
+// Arguments below -1000 are raised to -1000 (the result is 0 either way);
+// NaN passes through.
+constexpr double kExp11[12] = {
+    1.0, 1.0, 0.5000000000000001,
+    0.16666666666666669, 0.04166666666662416, 0.008333333333330063,
+    0.0013888888917199863, 0.00019841269863042963, 2.4801521317484083e-05,
+    2.7557268476553695e-06, 2.7620078203806394e-07, 2.5100377619606372e-08};
 HGKS_FN double exp_cw(double x) {
   x = x < -1000.0 ? -1000.0 : x;
   const double k = rint(x * kconst<double>(1.4426950408889634));  // 1/ln2
   double r = fma(-k, 0.693146705627441406250, x);                 // ln2 hi
   r = fma(-k, kconst<double>(4.7493250390316727e-07), r);          // ln2 lo
-  double p = kconst<double>(exp_taylor_coef(13));
+  double p = kconst<double>(kExp11[11]);
 #pragma unroll
-  for (int n = 12; n >= 0; --n) p = fma(p, r, kconst<double>(exp_taylor_coef(n)));
+  for (int n = 10; n >= 0; --n) p = fma(p, r, kconst<double>(kExp11[n]));
   return ldexp(p, (int)k);
 }
 
@@ -59,22 +61,27 @@ template <> HGKS_FN double d_exp<double>(double x) {
 #endif
 }
 template <> HGKS_FN float d_exp<float>(float x) { return expf(x); }
-// erf(x) = (2/sqrt(pi)) sum_n (-1)^n x^(2n+1) / (n! (2n+1)), its Maclaurin
-// series, summed by Horner's rule in x^2 over the first N terms.  For
-// |x| <= 1 the first omitted term is below 5e-18 with N = 18 (double) and
-// 1.2e-9 with N = 11 (float).
-constexpr double erf_series_coef(int n) {
-  double f = 1.12837916709551257389615890312154517;  // 2/sqrt(pi)
-  for (int k = 1; k <= n; ++k) f = -f / k;
-  return f / (2 * n + 1);
-}
+// erf(x) / x for |x| <= 1 as a polynomial in x^2 that interpolates its
+// Maclaurin series at the Chebyshev nodes of [0, 1] (computed in 60 digits):
+// relative error 1.6e-17 with 13 coefficients (double) and 1.4e-9 with 7
+// (float), where the truncated series took 18 and 11.
+constexpr double kErf12[13] = {
+    1.1283791670955126, -0.3761263890318375, 0.11283791670954879,
+    -0.026866170645076792, 0.0052239776248180145, -0.000854832698083379,
+    0.0001205533111164271, -1.4925595266831182e-05, 1.6461000484121368e-06,
+    -1.6350312701054695e-07, 1.4659775274047436e-08, -1.1372848856791674e-09,
+    5.957176147748911e-11};
+constexpr double kErf6[7] = {
+    1.1283791658483509, -0.37612626666720334, 0.11283594715160218,
+    -0.026854212010626412, 0.005189087423433974, -0.000801686428716587,
+    7.875875062685488e-05};
 
 template <int N, typename T>
-HGKS_FN T erf_series(T x) {
+HGKS_FN T erf_small(T x, const double (&c)[N]) {
   const T t = x * x;
-  T s = T(erf_series_coef(N - 1));
+  T s = T(c[N - 1]);
 #pragma unroll
-  for (int n = N - 2; n >= 0; --n) s = s * t + kconst<T>(erf_series_coef(n));
+  for (int n = N - 2; n >= 0; --n) s = s * t + kconst<T>(c[n]);
   return s * x;
 }
 
@@ -114,18 +121,18 @@ HGKS_FN T erfc_tail(T y, T e, const double (&c)[N]) {
   return e * p * (a * r);
 }
 
-// erfc(x) given e = exp(-x^2): 1 - erf by the series where |x| <= 1 (every
+// erfc(x) given e = exp(-x^2): 1 - erf by the polynomial where |x| <= 1 (every
 // smooth-flow interface state has |sqrt(lambda) U| well below 1), the tail
 // form elsewhere.  The library erfc it replaces forms its own exponential
 // and kept some 160 instructions and their registers in each side's code.
 template <typename T> HGKS_FN T d_erfc(T x, T e);
 template <> HGKS_FN double d_erfc<double>(double x, double e) {
-  if (fabs(x) <= 1.0) return 1.0 - erf_series<18>(x);
+  if (fabs(x) <= 1.0) return 1.0 - erf_small(x, kErf12);
   const double t = erfc_tail(fabs(x), e, kErfcx20);
   return x > 0.0 ? t : 2.0 - t;
 }
 template <> HGKS_FN float d_erfc<float>(float x, float e) {
-  if (fabsf(x) <= 1.0f) return 1.0f - erf_series<11>(x);
+  if (fabsf(x) <= 1.0f) return 1.0f - erf_small(x, kErf6);
   const float t = erfc_tail(fabsf(x), e, kErfcx9);
   return x > 0.0f ? t : 2.0f - t;
 }

@@ -84,7 +84,7 @@ struct GasParams {
 // slot[64 k] (slot: the lane's own column of its wave's area, which no other
 // lane touches), so that they hold no registers while the right side is
 // formed.
-constexpr int kParked = 13;
+constexpr int kParked = 12;
 
 template <typename T, bool PARK = false>
 struct FluxAcc {
@@ -344,7 +344,7 @@ HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>
 // loads into the left side's work, where both sides' values would be live
 // at once.
 template <typename T, bool PARK>
-__device__ __forceinline__ void after_left_side(size_t& idx, const FluxAcc<T, PARK>& A) {
+__device__ __forceinline__ void after_left_side(unsigned& idx, const FluxAcc<T, PARK>& A) {
   asm volatile("" : "+v"(idx) : "v"(A.X6[0]), "v"(A.X6[4]), "v"(A.Q0[4]), "v"(A.X4[4]));
 }
 

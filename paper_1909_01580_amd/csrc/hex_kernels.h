@@ -1311,7 +1311,7 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
       }
       side_terms<+1, PR, kAssignFirst<TC>>(W, dW, gp, acc);
     }
-    size_t iRt = iR;
+    unsigned iRt = (unsigned)iR;
     after_left_side(iRt, acc);
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("" ::: "memory");
@@ -1345,7 +1345,7 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
       to_local(val, grad, u, n0, n1, n2, W, dW);
       side_terms<+1, PR, kAssignFirst<TC>>(W, dW, gp, acc);
     }
-    size_t iRt = iR;
+    unsigned iRt = (unsigned)iR;
     after_left_side(iRt, acc);
     {
       asm volatile("" ::: "memory");
