@@ -211,26 +211,20 @@ HGKS_FN void sched_fence() {
 #endif
 }
 
-// Contributions of one side (sg = +1: left state, particles with u > 0;
-// sg = -1: right state, u < 0; sg may be a runtime value).  W: conservative
-// variables in the local frame; dW[j]: their derivatives along n_x, n_y,
-// n_z.  The side's pressure goes to pside.  FIRST: the first side of the
+// Contributions of one side (SIDE = +1: left state, particles with u > 0;
+// -1: right state, u < 0).  P: the primitive state in the local frame; d[j]:
+// its derivatives along n_x, n_y, n_z.  FIRST: the first side of the
 // pair, whose terms are assigned to the sums rather than added to zeroed
 // ones (the same values; an add to 0.0 cannot be dropped by the compiler,
 // whereas here no zeroing or add is issued).
-template <bool PR = false, bool FIRST = false, typename T, bool PARK>
-HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams<T>& g, T sg, FluxAcc<T, PARK>& A,
-                          T& pside) {
+template <int SIDE, bool PR = false, bool FIRST = false, typename T, bool PARK>
+HGKS_FN void side_core(const Prim<T>& P, const PGrad<T> (&d)[3], const GasParams<T>& g, FluxAcc<T, PARK>& A) {
   constexpr bool ACC = !FIRST;
-  Prim<T> P;
-  primitives(Wc, g, P);
+  const T sg = T(SIDE);
   const T U = P.U, V = P.V, W = P.W, h = P.h;
   const T uu = U * U;
   const T k2t = T(0.5) * (V * V + W * W);  // tangential kinetic energy
   const T et = k2t + g.K2h * h;            // mean of (v^2 + w^2 + xi^2) / 2
-  PGrad<T> d[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) prim_grad(dW[j], P, k2t + T(0.5) * uu, g, d[j]);
 
   // half-line moments
   const T lam = T(0.5) * P.il;
@@ -319,12 +313,20 @@ HGKS_FN void side_terms_s(const T (&Wc)[5], const T (&dW)[3][5], const GasParams
       put<ACC>(A.S5[4], f0 * (tx * (g.K4h * h + g.K2h * uu) - Dh * (g.K2h * U)) + k2t * n0 + V * y0 + W * w0);
     }
   }
-  pside = P.p;
+  A.p[SIDE > 0 ? 0 : 1] = P.p;
 }
 
+// The same from the conservative variables W in the local frame and their
+// derivatives dW[j] along n_x, n_y, n_z.
 template <int SIDE, bool PR = false, bool FIRST = false, typename T, bool PARK>
 HGKS_FN void side_terms(const T (&W)[5], const T (&dW)[3][5], const GasParams<T>& g, FluxAcc<T, PARK>& A) {
-  side_terms_s<PR, FIRST>(W, dW, g, T(SIDE), A, A.p[SIDE > 0 ? 0 : 1]);
+  Prim<T> P;
+  primitives(W, g, P);
+  const T k2 = T(0.5) * (P.U * P.U + P.V * P.V + P.W * P.W);
+  PGrad<T> d[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) prim_grad(dW[j], P, k2, g, d[j]);
+  side_core<SIDE, PR, FIRST>(P, d, g, A);
 }
 
 // Register budget of the flux kernels: three waves per SIMD (168 registers

@@ -916,25 +916,49 @@ __global__ void __launch_bounds__(kBlock) k_posit_exact_hex(HexGrid H, const dou
 }
 
 // ---------------------------------------------------------------- K3
-// Value and physical gradient of the five variables of cell idx at the
-// physical point x (centroid shifted by `shift` for periodic images), in
-// the compute type: the scaled coordinates are formed in double (absolute
-// positions), the polynomial is evaluated in TC.  A first-order fallback
-// point gives the cell mean and zero gradient (Sec. 4).  cv points at the
-// cell's 50 rows, kCB values apart: in the coefficient array or in a staged
-// copy with the same row stride.
+// Scaled position of the point x in cell idx (its centroid shifted by
+// `shift` for periodic images), formed in double (absolute positions), the
+// basis' second moments, and 1/h, in the compute type.
 template <typename TC>
-__device__ __forceinline__ void eval_hex_rows(const TC* cv, const double* __restrict__ geo, size_t N, size_t idx,
-                                              const double (&shift)[3], const double (&x)[3], bool fb, TC (&val)[5],
-                                              TC (&grad)[5][3]) {
+__device__ __forceinline__ void hex_local(const double* __restrict__ geo, size_t N, size_t idx,
+                                          const double (&shift)[3], const double (&x)[3], TC (&X)[3], TC (&b2)[6],
+                                          TC& ih) {
   HexCell C;
   load_cell(geo, N, idx, C);
-  TC X[3], m[6];
 #pragma unroll
   for (int e = 0; e < 3; ++e) X[e] = TC((x[e] - C.c[e] - shift[e]) * C.ih);
 #pragma unroll
-  for (int e = 0; e < 6; ++e) m[e] = TC(C.m[e]);
-  const TC ih = TC(C.ih);
+  for (int e = 0; e < 3; ++e) b2[e] = X[e] * X[e] - TC(C.m[e]);
+  b2[3] = X[0] * X[1] - TC(C.m[3]);
+  b2[4] = X[1] * X[2] - TC(C.m[4]);
+  b2[5] = X[0] * X[2] - TC(C.m[5]);
+  ih = TC(C.ih);
+}
+
+// Quadratic about q with coefficients c: value, and gradient per scaled
+// coordinate (the physical one is ih times it).
+template <typename TC>
+__device__ __forceinline__ void hex_quad(TC q, const TC (&c)[9], const TC (&X)[3], const TC (&b2)[6], TC& val,
+                                         TC (&g)[3]) {
+  const TC x2 = TC(2) * X[0], y2 = TC(2) * X[1], z2 = TC(2) * X[2];
+  val = q + c[0] * X[0] + c[1] * X[1] + c[2] * X[2] + c[3] * b2[0] + c[4] * b2[1] + c[5] * b2[2] + c[6] * b2[3] +
+        c[7] * b2[4] + c[8] * b2[5];
+  g[0] = c[0] + c[3] * x2 + c[6] * X[1] + c[8] * X[2];
+  g[1] = c[1] + c[4] * y2 + c[6] * X[0] + c[7] * X[2];
+  g[2] = c[2] + c[5] * z2 + c[8] * X[0] + c[7] * X[1];
+}
+
+// Value and gradient (per scaled coordinate) of the five variables of cell
+// idx at the physical point x.  A first-order fallback point gives the cell
+// mean and zero gradient (Sec. 4).  cv points at the cell's 50 rows, kCB
+// values apart: in the coefficient array or in a staged copy with the same
+// row stride.
+template <typename TC>
+__device__ __forceinline__ void eval_hex_rows(const TC* cv, const double* __restrict__ geo, size_t N, size_t idx,
+                                              const double (&shift)[3], const double (&x)[3], bool fb, TC (&val)[5],
+                                              TC (&grad)[5][3], TC& ih) {
+  TC X[3], b2[6];
+  hex_local(geo, N, idx, shift, x, X, b2, ih);
   constexpr int CB = kCB<TC>;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
@@ -942,13 +966,7 @@ __device__ __forceinline__ void eval_hex_rows(const TC* cv, const double* __rest
     TC c[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) c[e] = ck[(e + 1) * CB];
-    const TC q0 = ck[0];
-    val[v] = q0 + c[0] * X[0] + c[1] * X[1] + c[2] * X[2] + c[3] * (X[0] * X[0] - m[0]) +
-             c[4] * (X[1] * X[1] - m[1]) + c[5] * (X[2] * X[2] - m[2]) + c[6] * (X[0] * X[1] - m[3]) +
-             c[7] * (X[1] * X[2] - m[4]) + c[8] * (X[0] * X[2] - m[5]);
-    grad[v][0] = (c[0] + TC(2) * c[3] * X[0] + c[6] * X[1] + c[8] * X[2]) * ih;
-    grad[v][1] = (c[1] + TC(2) * c[4] * X[1] + c[6] * X[0] + c[7] * X[2]) * ih;
-    grad[v][2] = (c[2] + TC(2) * c[5] * X[2] + c[8] * X[0] + c[7] * X[1]) * ih;
+    hex_quad(ck[0], c, X, b2, val[v], grad[v]);
   }
   if (fb) {
     asm volatile("");
@@ -963,8 +981,8 @@ __device__ __forceinline__ void eval_hex_rows(const TC* cv, const double* __rest
 template <typename TC>
 __device__ __forceinline__ void eval_hex(const TC* __restrict__ coef, const double* __restrict__ geo, size_t N,
                                          size_t idx, const double (&shift)[3], const double (&x)[3], bool fb,
-                                         TC (&val)[5], TC (&grad)[5][3]) {
-  eval_hex_rows(coef + coef_cell<TC>(idx), geo, N, idx, shift, x, fb, val, grad);
+                                         TC (&val)[5], TC (&grad)[5][3], TC& ih) {
+  eval_hex_rows(coef + coef_cell<TC>(idx), geo, N, idx, shift, x, fb, val, grad, ih);
 }
 
 // Frame of Sec. 3 at the face point P: n along X_a x X_b, t2 along X_b,
@@ -993,22 +1011,17 @@ __device__ __forceinline__ void face_centre_frame(const HexGrid& H, int D, int c
   face_frame(P, n, t1, t2);
 }
 
-// Value and physical gradient of the five conservative variables at the
-// physical point x of the cell reconstructed in characteristic variables:
-// cv points at the cell in its face array, B holds the face's eigenvectors.
-// A first-order fallback point gives the cell mean and zero gradient.
+// Value and gradient (per scaled coordinate) of the five conservative
+// variables at the physical point x of the cell reconstructed in
+// characteristic variables: cv points at the cell in its face array, B
+// holds the face's eigenvectors.  A first-order fallback point gives the
+// cell mean and zero gradient.
 template <typename TC>
 __device__ __forceinline__ void eval_char_hex(const TC* __restrict__ cv, const double* __restrict__ geo, size_t N,
                                               size_t idx, const double (&shift)[3], const double (&x)[3], bool fb,
-                                              const CharFrame& B, TC (&val)[5], TC (&grad)[5][3]) {
-  HexCell C;
-  load_cell(geo, N, idx, C);
-  TC X[3], m[6];
-#pragma unroll
-  for (int e = 0; e < 3; ++e) X[e] = TC((x[e] - C.c[e] - shift[e]) * C.ih);
-#pragma unroll
-  for (int e = 0; e < 6; ++e) m[e] = TC(C.m[e]);
-  const TC ih = TC(C.ih);
+                                              const CharFrame& B, TC (&val)[5], TC (&grad)[5][3], TC& ih) {
+  TC X[3], b2[6];
+  hex_local(geo, N, idx, shift, x, X, b2, ih);
   constexpr int CB = kCB<TC>;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
@@ -1022,13 +1035,8 @@ __device__ __forceinline__ void eval_char_hex(const TC* __restrict__ cv, const d
     TC c[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) c[e] = ck[(e + 1) * CB];
-    const TC du = c[0] * X[0] + c[1] * X[1] + c[2] * X[2] + c[3] * (X[0] * X[0] - m[0]) +
-                  c[4] * (X[1] * X[1] - m[1]) + c[5] * (X[2] * X[2] - m[2]) + c[6] * (X[0] * X[1] - m[3]) +
-                  c[7] * (X[1] * X[2] - m[4]) + c[8] * (X[0] * X[2] - m[5]);
-    TC g[3];
-    g[0] = (c[0] + TC(2) * c[3] * X[0] + c[6] * X[1] + c[8] * X[2]) * ih;
-    g[1] = (c[1] + TC(2) * c[4] * X[1] + c[6] * X[0] + c[7] * X[2]) * ih;
-    g[2] = (c[2] + TC(2) * c[5] * X[2] + c[8] * X[0] + c[7] * X[1]) * ih;
+    TC du, g[3];
+    hex_quad(TC(0), c, X, b2, du, g);
     double r[5];
     char_rcol(B, f, r);
 #pragma unroll
@@ -1041,56 +1049,44 @@ __device__ __forceinline__ void eval_char_hex(const TC* __restrict__ cv, const d
   }
 }
 
-// Conservative variables seen from a frame moving with u (one vector, also
-// applied to the gradients), then rotated into the frame (nx, ny, nz); in
-// the compute type.
+// Primitive state and its derivatives in the frame (nx, ny, nz) moving with
+// the velocity u, from the conservative variables and their gradients per
+// scaled coordinate in the fixed frame.  The derivatives of the primitive
+// state do not see the frame's velocity and only their velocity part turns
+// with its axes, so they are formed from the directional derivatives of the
+// fixed-frame variables and neither a shift nor a rotation of conservative
+// gradients is needed.
 template <typename TC>
-__device__ __forceinline__ void to_local(const TC (&val)[5], const TC (&grad)[5][3], const double (&ud)[3],
+__device__ __forceinline__ void to_local(const TC (&val)[5], const TC (&grad)[5][3], TC ih, const double (&ud)[3],
                                          const double (&nxd)[3], const double (&nyd)[3], const double (&nzd)[3],
-                                         TC (&W)[5], TC (&dW)[3][5]) {
-  TC u[3], n[3][3];
+                                         const GasParams<TC>& gp, Prim<TC>& P, PGrad<TC> (&d)[3]) {
+  TC n[3][3];
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
-    u[e] = TC(ud[e]);
     n[0][e] = TC(nxd[e]);
     n[1][e] = TC(nyd[e]);
     n[2][e] = TC(nzd[e]);
   }
-  const TC uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-  // shifted values
-  TC s[5];
-  s[0] = val[0];
-  TC Mu = TC(0);
-#pragma unroll
-  for (int e = 0; e < 3; ++e) {
-    s[1 + e] = val[1 + e] - val[0] * u[e];
-    Mu += val[1 + e] * u[e];
-  }
-  s[4] = val[4] - Mu + TC(0.5) * val[0] * uu;
-  W[0] = s[0];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) W[1 + j] = s[1] * n[j][0] + s[2] * n[j][1] + s[3] * n[j][2];
-  W[4] = s[4];
-  // gradients: derivative along n_j of the shifted variables
+  primitives(val, gp, P);
+  const TC k2 = TC(0.5) * (P.U * P.U + P.V * P.V + P.W * P.W);
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    TC g[5];
+    const TC s[3] = {n[j][0] * ih, n[j][1] * ih, n[j][2] * ih};
+    TC b[5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) g[v] = grad[v][0] * n[j][0] + grad[v][1] * n[j][1] + grad[v][2] * n[j][2];
-    TC gs[5];
-    gs[0] = g[0];
-    TC gMu = TC(0);
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      gs[1 + e] = g[1 + e] - g[0] * u[e];
-      gMu += g[1 + e] * u[e];
-    }
-    gs[4] = g[4] - gMu + TC(0.5) * g[0] * uu;
-    dW[j][0] = gs[0];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) dW[j][1 + r] = gs[1] * n[r][0] + gs[2] * n[r][1] + gs[3] * n[r][2];
-    dW[j][4] = gs[4];
+    for (int v = 0; v < 5; ++v) b[v] = grad[v][0] * s[0] + grad[v][1] * s[1] + grad[v][2] * s[2];
+    PGrad<TC> q;
+    prim_grad(b, P, k2, gp, q);
+    d[j].r = q.r;
+    d[j].th = q.th;
+    d[j].mx = q.mx * n[0][0] + q.my * n[0][1] + q.mz * n[0][2];
+    d[j].my = q.mx * n[1][0] + q.my * n[1][1] + q.mz * n[1][2];
+    d[j].mz = q.mx * n[2][0] + q.my * n[2][1] + q.mz * n[2][2];
   }
+  const TC U[3] = {P.U - TC(ud[0]), P.V - TC(ud[1]), P.W - TC(ud[2])};
+  P.U = U[0] * n[0][0] + U[1] * n[0][1] + U[2] * n[0][2];
+  P.V = U[0] * n[1][0] + U[1] * n[1][1] + U[2] * n[1][2];
+  P.W = U[0] * n[2][0] + U[1] * n[2][1] + U[2] * n[2][2];
 }
 
 // Local-frame flux vector back to global components and to the fixed frame.
@@ -1106,15 +1102,21 @@ __device__ __forceinline__ void to_global(const double (&f)[5], const double (&u
   g[4] = f[4] + (M[0] * u[0] + M[1] * u[1] + M[2] * u[2]) + 0.5 * uu * f[0];
 }
 
-// Rows of the flux kernel's per-lane LDS slot: the Gauss point's geometry
-// (18), and with per-face reconstructions (characteristic variables) the
+// The flux kernel's LDS: per lane the Gauss point's geometry (18 doubles),
+// and with per-face reconstructions (characteristic variables) per face the
 // face-centre frame (9) and the face's mean state (5).
+constexpr int kHexStash = 18, kHexFaceStash = 14;
+
 template <bool FS>
-constexpr int kHexStash = FS ? 32 : 18;
+struct HexStash {
+  double p[kHexStash][kFluxLanes];
+  double f[FS ? kHexFaceStash : 1][FS ? kFluxLanes / 4 : 1];
+};
 
 // One lane = one Gauss point of one face normal to axis D (uniform over the
-// workgroup); lane l of block lb takes Gauss point l % 4 of face slot l / 4
-// in the flux block order of the box kernels (face_of_block).
+// workgroup); lane l of part `sub` of block lb takes Gauss point l % 4 of
+// face slot sub kFluxLanes / 4 + l / 4 in the flux block order of the box
+// kernels (wave_face).
 // PR: the extended viscous model (viscosity law, Prandtl correction); FS:
 // per-face coefficient arrays (reconstruction in characteristic variables),
 // H.box.fs_stride elements apart.
@@ -1122,21 +1124,24 @@ template <typename TC, bool PR = false, bool FS = false>
 __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __restrict__ coef,
                                               const double* __restrict__ geo, const uint32_t* __restrict__ mask,
                                               TC* __restrict__ face, double* __restrict__ vface,
-                                              const GasParams<TC>& gp, TC dt, TC idt, size_t N, unsigned lb, int D,
-                                              double (&stash)[kHexStash<FS>][kBlock], TC* stage = nullptr) {
+                                              const GasParams<TC>& gp, TC dt, TC idt, size_t N, unsigned lb,
+                                              unsigned sub, int D, HexStash<FS>& stash, TC* stage = nullptr) {
   const int gpi = (int)(threadIdx.x & 3);
-  int c[3];
-  size_t f;
-  const bool live = face_of_block(H.box, D, lb, threadIdx.x >> 2, c, f);
+  const unsigned fslot = threadIdx.x >> 2;
   // Face on the lower side of cell c along D: plane c[D] (c[d] in [0, n_d)
   // for every lane, dead ones included).
+  FaceLane fl;
   double cx[4][3], cu[4][3];
-  if (D == 0)
-    face_corners_in<0>(H, c, cx, cu);
-  else if (D == 1)
-    face_corners_in<1>(H, c, cx, cu);
-  else
-    face_corners_in<2>(H, c, cx, cu);
+  if (D == 0) {
+    fl = wave_face<0>(H.box, lb, sub * (kFluxLanes / 4), fslot);
+    face_corners_in<0>(H, fl.c, cx, cu);
+  } else if (D == 1) {
+    fl = wave_face<1>(H.box, lb, sub * (kFluxLanes / 4), fslot);
+    face_corners_in<1>(H, fl.c, cx, cu);
+  } else {
+    fl = wave_face<2>(H.box, lb, sub * (kFluxLanes / 4), fslot);
+    face_corners_in<2>(H, fl.c, cx, cu);
+  }
   FacePoint Pt;
   face_point(cx, cu, (gpi >> 1) ? kGaussNode : -kGaussNode, (gpi & 1) ? kGaussNode : -kGaussNode, Pt);
   double av[3], adot[3], t1[3], t2[3];
@@ -1160,30 +1165,32 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
   // registers across the two sides' gas-kinetic terms: x, u, the frame,
   // area, d|a|/dt rate and the volume rate.
   {
-    double* g = &stash[0][threadIdx.x];
+    double* g = &stash.p[0][threadIdx.x];
+    constexpr int L = kFluxLanes;
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
-      g[(0 + e) * kBlock] = Pt.x[e];
-      g[(3 + e) * kBlock] = Pt.u[e];
-      g[(6 + e) * kBlock] = nx[e];
-      g[(9 + e) * kBlock] = ny[e];
-      g[(12 + e) * kBlock] = nz[e];
+      g[(0 + e) * L] = Pt.x[e];
+      g[(3 + e) * L] = Pt.u[e];
+      g[(6 + e) * L] = nx[e];
+      g[(9 + e) * L] = ny[e];
+      g[(12 + e) * L] = nz[e];
     }
-    g[15 * kBlock] = area;
-    g[16 * kBlock] = Pt.u[0] * adot[0] + Pt.u[1] * adot[1] + Pt.u[2] * adot[2];
-    g[17 * kBlock] = 0.25 * (Pt.u[0] * av[0] + Pt.u[1] * av[1] + Pt.u[2] * av[2]);
+    g[15 * L] = area;
+    g[16 * L] = Pt.u[0] * adot[0] + Pt.u[1] * adot[1] + Pt.u[2] * adot[2];
+    g[17 * L] = 0.25 * (Pt.u[0] * av[0] + Pt.u[1] * av[1] + Pt.u[2] * av[2]);
     if constexpr (FS) {
       // the frame at the face centre, the projection frame of both cells'
-      // reconstructions for this face
+      // reconstructions for this face (the face's four lanes write the
+      // same values)
       FacePoint Pc;
       face_point(cx, cu, 0.0, 0.0, Pc);
       double fn[3], f1[3], f2[3];
       face_frame(Pc, fn, f1, f2);
 #pragma unroll
       for (int e = 0; e < 3; ++e) {
-        g[(18 + e) * kBlock] = fn[e];
-        g[(21 + e) * kBlock] = f1[e];
-        g[(24 + e) * kBlock] = f2[e];
+        stash.f[e][fslot] = fn[e];
+        stash.f[3 + e][fslot] = f1[e];
+        stash.f[6 + e][fslot] = f2[e];
       }
     }
   }
@@ -1191,26 +1198,20 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
   // (no instruction): the fence keeps the compiler from forwarding the
   // stored registers, and unlike a volatile access it leaves the loads
   // free to be issued together with the others.
-  const double* gs = &stash[0][threadIdx.x];
+  const double* gs = &stash.p[0][threadIdx.x];
   auto get3 = [&](int k, double (&v)[3]) {
 #pragma unroll
-    for (int e = 0; e < 3; ++e) v[e] = gs[(k + e) * kBlock];
+    for (int e = 0; e < 3; ++e) v[e] = gs[(k + e) * kFluxLanes];
   };
 
   // The two cells: c itself (in range, no shift) and its lower neighbour
   // along D, which wraps to the last plane, shifted back by the period,
   // where c[D] = 0.
   double shL[3] = {0.0, 0.0, 0.0}, shR[3] = {0.0, 0.0, 0.0};
-  size_t iL, iR;
+  const unsigned iL = fl.iL, iR = fl.iR;
   {
-    const unsigned s1 = (unsigned)H.n[0], s2 = s1 * (unsigned)H.n[1];
-    const unsigned r = (unsigned)c[0] + (unsigned)c[1] * s1 + (unsigned)c[2] * s2;
-    const unsigned sD = D == 0 ? 1u : (D == 1 ? s1 : s2);
-    const int cD = D == 0 ? c[0] : (D == 1 ? c[1] : c[2]);
-    const bool wrap = cD == 0;
-    iR = r;
-    iL = wrap ? r + (unsigned)(H.n[D] - 1) * sD : r - sD;
-    const double sh = wrap ? -H.period[D] : 0.0;
+    const int cD = D == 0 ? fl.c[0] : (D == 1 ? fl.c[1] : fl.c[2]);
+    const double sh = cD == 0 ? -H.period[D] : 0.0;
     shL[0] = D == 0 ? sh : 0.0;
     shL[1] = D == 1 ? sh : 0.0;
     shL[2] = D == 2 ? sh : 0.0;
@@ -1227,160 +1228,125 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
     const TC* mL = coefL + coef_cell<TC>(iL);
     const TC* mR = coefR + coef_cell<TC>(iR);
 #pragma unroll
-    for (int v = 0; v < 5; ++v)
-      stash[27 + v][threadIdx.x] = 0.5 * ((double)mL[10 * v * CB] + (double)mR[10 * v * CB]);
+    for (int v = 0; v < 5; ++v) stash.f[9 + v][fslot] = 0.5 * ((double)mL[10 * v * CB] + (double)mR[10 * v * CB]);
   }
-  auto eval_side = [&](const TC* cf, size_t icell, const double (&sh)[3], const double (&x)[3], bool fb,
-                       TC (&val)[5], TC (&grad)[5][3]) {
+  FluxAcc<TC> acc;
+  acc_begin(acc);
+  // State of one side and its derivatives in the point's frame; cv: the
+  // cell's rows.
+  auto side = [&](const TC* cv, unsigned icell, const double (&sh)[3], bool fb, Prim<TC>& P, PGrad<TC> (&d)[3]) {
+    asm volatile("" ::: "memory");
+    double x[3], u[3], n0[3], n1[3], n2[3];
+    get3(0, x);
+    TC val[5], grad[5][3], ih;
     if constexpr (FS) {
       CharFrame B;
       {
         double fn[3], f1[3], f2[3], Qb[5];
-        get3(18, fn);
-        get3(21, f1);
-        get3(24, f2);
 #pragma unroll
-        for (int v = 0; v < 5; ++v) Qb[v] = gs[(27 + v) * kBlock];
+        for (int e = 0; e < 3; ++e) {
+          fn[e] = stash.f[e][fslot];
+          f1[e] = stash.f[3 + e][fslot];
+          f2[e] = stash.f[6 + e][fslot];
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Qb[v] = stash.f[9 + v][fslot];
         char_frame(Qb, fn, f1, f2, gp.gamma, B);
       }
-      eval_char_hex(cf + coef_cell<TC>(icell), geo, N, icell, sh, x, fb, B, val, grad);
+      eval_char_hex(cv, geo, N, icell, sh, x, fb, B, val, grad, ih);
     } else {
-      eval_hex(cf, geo, N, icell, sh, x, fb, val, grad);
+      eval_hex_rows(cv, geo, N, icell, sh, x, fb, val, grad, ih);
     }
+    get3(3, u);
+    get3(6, n0);
+    get3(9, n1);
+    get3(12, n2);
+    to_local(val, grad, ih, u, n0, n1, n2, gp, P, d);
   };
-
-  FluxAcc<TC> acc;
-  acc_begin(acc);
   if constexpr (std::is_same<TC, float>::value) {
     // FP32: both sides' local states first, then the side terms; the
-    // accumulators are not live while the coefficients are loaded (113
-    // registers, no spills, 7% faster).  In FP64 this order is 11% slower
-    // than the sides one after the other with the right cell's loads
-    // deferred, below.
-    TC WL[5], dWL[3][5], WR[5], dWR[3][5];
-    {
-      asm volatile("" ::: "memory");
-      double x[3], u[3], n0[3], n1[3], n2[3];
-      get3(0, x);
-      get3(3, u);
-      get3(6, n0);
-      get3(9, n1);
-      get3(12, n2);
-      TC val[5], grad[5][3];
-      eval_side(coefL, iL, shL, x, fbL, val, grad);
-      to_local(val, grad, u, n0, n1, n2, WL, dWL);
-      eval_side(coefR, iR, shR, x, fbR, val, grad);
-      to_local(val, grad, u, n0, n1, n2, WR, dWR);
-    }
-    side_terms<+1, PR, kAssignFirst<TC>>(WL, dWL, gp, acc);
-    side_terms<-1, PR>(WR, dWR, gp, acc);
+    // accumulators are not live while the coefficients are loaded.  In FP64
+    // the sides follow one another, the right cell's loads deferred.
+    Prim<TC> PL, PR_;
+    PGrad<TC> dL[3], dR[3];
+    side(coefL + coef_cell<TC>(iL), iL, shL, fbL, PL, dL);
+    side(coefR + coef_cell<TC>(iR), iR, shR, fbR, PR_, dR);
+    side_core<+1, PR, kAssignFirst<TC>>(PL, dL, gp, acc);
+    side_core<-1, PR>(PR_, dR, gp, acc);
   } else if constexpr (!FS) {
     // FP64: the right cells' coefficients are staged in LDS by direct
     // loads issued after the left cell's values have arrived, as in the box
     // flux (the same [50 rows][8 faces] groups of 64-byte rows), and read
     // from there after the left side's terms; the right cell's geometry
     // comes from global memory as before.
-    static_assert(sizeof(TC) == 8 && kCB<TC> == 8, "rows of 8 doubles");
-    const unsigned l = threadIdx.x & 63u;
-    TC* rs = stage + (threadIdx.x >> 6) * 2 * kStageGroup;
-    unsigned cell0 = __shfl((unsigned)iR, (int)(((l >> 1) & 7u) * 4u));
-    unsigned cell1 = __shfl((unsigned)iR, (int)((8u + ((l >> 1) & 7u)) * 4u));
+    static_assert(sizeof(TC) == 8 && kCB<TC> == 8 && kFluxLanes == 64, "rows of 8 doubles, one wave");
+    const unsigned l = threadIdx.x;
+    unsigned cell0 = __shfl(iR, (int)(((l >> 1) & 7u) * 4u));
+    unsigned cell1 = __shfl(iR, (int)((8u + ((l >> 1) & 7u)) * 4u));
     {
-      asm volatile("" ::: "memory");
-      double x[3], u[3], n0[3], n1[3], n2[3];
-      get3(0, x);
-      get3(3, u);
-      get3(6, n0);
-      get3(9, n1);
-      get3(12, n2);
-      TC val[5], grad[5][3];
-      eval_hex(coefL, geo, N, iL, shL, x, fbL, val, grad);
-      TC W[5], dW[3][5];
-      to_local(val, grad, u, n0, n1, n2, W, dW);
-      asm volatile("" : "+v"(cell0), "+v"(cell1) : "v"(W[0]), "v"(dW[2][4]));
+      Prim<TC> P;
+      PGrad<TC> d[3];
+      side(coefL + coef_cell<TC>(iL), iL, shL, fbL, P, d);
+      asm volatile("" : "+v"(cell0), "+v"(cell1) : "v"(P.U), "v"(d[2].th));
       const unsigned lane = (l >> 4) * 64 + (l & 1u) * 4;
       const GlobalPtr s0 = (GlobalPtr)((const char*)(coefR + coef_cell<TC>(cell0)) + lane);
       const GlobalPtr s1 = (GlobalPtr)((const char*)(coefR + coef_cell<TC>(cell1)) + lane);
-      const LdsPtr d0 = (LdsPtr)rs;
-      const LdsPtr d1 = (LdsPtr)(rs + kStageGroup);
+      const LdsPtr d0 = (LdsPtr)stage;
+      const LdsPtr d1 = (LdsPtr)(stage + kStageGroup);
       copy_pieces<0, 12>(s0, d0);
       copy_pieces<0, 12>(s1, d1);
       if (l < 32u) {
         copy_pieces<12, 13>(s0, d0);
         copy_pieces<12, 13>(s1, d1);
       }
-      side_terms<+1, PR, kAssignFirst<TC>>(W, dW, gp, acc);
+      side_core<+1, PR, kAssignFirst<TC>>(P, d, gp, acc);
     }
-    unsigned iRt = (unsigned)iR;
+    unsigned iRt = iR;
     after_left_side(iRt, acc);
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("" ::: "memory");
     {
-      const unsigned slot = threadIdx.x >> 2 & 15u;
-      const TC* cv = rs + (slot >> 3) * kStageGroup + (slot & 7u);
-      double x[3], u[3], n0[3], n1[3], n2[3];
-      get3(0, x);
-      get3(3, u);
-      get3(6, n0);
-      get3(9, n1);
-      get3(12, n2);
-      TC val[5], grad[5][3];
-      eval_hex_rows(cv, geo, N, iRt, shR, x, fbR, val, grad);
-      TC W[5], dW[3][5];
-      to_local(val, grad, u, n0, n1, n2, W, dW);
-      side_terms<-1, PR>(W, dW, gp, acc);
+      Prim<TC> P;
+      PGrad<TC> d[3];
+      side(stage + (fslot >> 3) * kStageGroup + (fslot & 7u), iRt, shR, fbR, P, d);
+      side_core<-1, PR>(P, d, gp, acc);
     }
   } else {
     {
-      asm volatile("" ::: "memory");
-      double x[3], u[3], n0[3], n1[3], n2[3];
-      get3(0, x);
-      get3(3, u);
-      get3(6, n0);
-      get3(9, n1);
-      get3(12, n2);
-      TC val[5], grad[5][3];
-      eval_side(coefL, iL, shL, x, fbL, val, grad);
-      TC W[5], dW[3][5];
-      to_local(val, grad, u, n0, n1, n2, W, dW);
-      side_terms<+1, PR, kAssignFirst<TC>>(W, dW, gp, acc);
+      Prim<TC> P;
+      PGrad<TC> d[3];
+      side(coefL + coef_cell<TC>(iL), iL, shL, fbL, P, d);
+      side_core<+1, PR, kAssignFirst<TC>>(P, d, gp, acc);
     }
-    unsigned iRt = (unsigned)iR;
+    unsigned iRt = iR;
     after_left_side(iRt, acc);
     {
-      asm volatile("" ::: "memory");
-      double x[3], u[3], n0[3], n1[3], n2[3];
-      get3(0, x);
-      get3(3, u);
-      get3(6, n0);
-      get3(9, n1);
-      get3(12, n2);
-      TC val[5], grad[5][3];
-      eval_side(coefR, iRt, shR, x, fbR, val, grad);
-      TC W[5], dW[3][5];
-      to_local(val, grad, u, n0, n1, n2, W, dW);
-      side_terms<-1, PR>(W, dW, gp, acc);
+      Prim<TC> P;
+      PGrad<TC> d[3];
+      side(coefR + coef_cell<TC>(iRt), iRt, shR, fbR, P, d);
+      side_core<-1, PR>(P, d, gp, acc);
     }
   }
+  pin_sums<PR>(acc);
   asm volatile("" ::: "memory");
+  TC Fl[5], dFl[5];
+  finish_flux<PR>(acc, gp, dt, idt, Fl, dFl);
   double u[3], n0[3], n1[3], n2[3];
   get3(3, u);
   get3(6, n0);
   get3(9, n1);
   get3(12, n2);
-  const double area2 = gs[15 * kBlock], rate = gs[16 * kBlock], vrate = gs[17 * kBlock];
-  TC Fl[5], dFl[5];
-  finish_flux<PR>(acc, gp, dt, idt, Fl, dFl);
-  double fl[5], dfl[5], q0l[5];
+  const double area2 = gs[15 * kFluxLanes], rate = gs[16 * kFluxLanes], vrate = gs[17 * kFluxLanes];
+  double fd[5], dfd[5], q0l[5];
 #pragma unroll
   for (int e = 0; e < 5; ++e) {
-    fl[e] = (double)Fl[e];
-    dfl[e] = (double)dFl[e];
+    fd[e] = (double)Fl[e];
+    dfd[e] = (double)dFl[e];
     q0l[e] = (double)acc.Q0[e];
   }
   double F[5], dF[5], Q0[5];
-  to_global(fl, u, n0, n1, n2, F);
-  to_global(dfl, u, n0, n1, n2, dF);
+  to_global(fd, u, n0, n1, n2, F);
+  to_global(dfd, u, n0, n1, n2, dF);
   to_global(q0l, u, n0, n1, n2, Q0);
   double out[12];
 #pragma unroll
@@ -1394,24 +1360,28 @@ __device__ __forceinline__ void flux_hex_face(const HexGrid& H, const TC* __rest
   for (int e = 0; e < 12; ++e) {
     out[e] = quad_xor_add<2>(quad_xor_add<1>(out[e]));
   }
-  if (live && gpi == 0) {
+  if (fl.live && gpi == 0) {
+    // 32-bit byte offsets from each row's uniform base
+    const unsigned fo = fl.f * (unsigned)sizeof(TC), vo = fl.f * 8u;
 #pragma unroll
-    for (int e = 0; e < 10; ++e) face[(size_t)e * N + f] = TC(out[e]);
-    vface[f] = out[10];
-    vface[N + f] = out[11];
+    for (int e = 0; e < 10; ++e) *(TC*)((char*)(face + (size_t)e * N) + fo) = TC(out[e]);
+    *(double*)((char*)vface + vo) = out[10];
+    *(double*)((char*)(vface + N) + vo) = out[11];
   }
 }
 
 // All faces of the three directions in one launch, nb blocks of 64 faces per
-// direction, interleaved (flux_block).  Register budget: two waves per SIMD
-// in FP64; four in FP32 (113 registers).
+// direction, interleaved (flux_block), one wave per workgroup as in the box
+// flux.  Register budget: two waves per SIMD in FP64; in FP32 four, with
+// per-face arrays three.
 template <typename TC, bool PR = false, bool FS = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 ? 2 : 4)))
+__global__ void __launch_bounds__(kFluxLanes)
+    __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 ? 2 : (FS ? 3 : 4))))
     k_flux_hex(HexGrid H, const TC* __restrict__ coef, const double* __restrict__ geo,
                const uint32_t* __restrict__ mask, TC* __restrict__ fx, TC* __restrict__ fy, TC* __restrict__ fz,
                double* __restrict__ vx, double* __restrict__ vy, double* __restrict__ vz, GasParams<TC> gp, TC dt,
                TC idt, size_t N, unsigned nb) {
-  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+  const unsigned p = xcd_block(blockIdx.x, gridDim.x), b = p / kFluxSubs, sub = p % kFluxSubs;
   if (b >= 3 * nb) return;
   const unsigned nbs[3] = {nb, nb, nb};
   int D;
@@ -1419,13 +1389,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(siz
   flux_block(b, nbs, D, lb);
   TC* face = D == 0 ? fx : (D == 1 ? fy : fz);
   double* vface = D == 0 ? vx : (D == 1 ? vy : vz);
-  __shared__ double stash[kHexStash<FS>][kBlock];
-  if constexpr (sizeof(TC) == 8 && !FS) {
-    __shared__ double stage[kBlock / 64 * 2 * kStageGroup];
-    flux_hex_face<TC, PR, FS>(H, coef, geo, mask, face, vface, gp, dt, idt, N, lb, D, stash, stage);
-  } else {
-    flux_hex_face<TC, PR, FS>(H, coef, geo, mask, face, vface, gp, dt, idt, N, lb, D, stash);
-  }
+  __shared__ HexStash<FS> stash;
+  __shared__ TC stage[sizeof(TC) == 8 && !FS ? 2 * kStageGroup : 1];
+  flux_hex_face<TC, PR, FS>(H, coef, geo, mask, face, vface, gp, dt, idt, N, lb, sub, D, stash, stage);
 }
 
 // ---------------------------------------------------------------- K4
@@ -1559,7 +1525,7 @@ __global__ void __launch_bounds__(kBlock) k_debug_gp_hex(HexGrid H, const TC* __
     face_corners(H, d, c[0], c[1], c[2], cx, cu);
     FacePoint P;
     face_point(cx, cu, (gp >> 1) ? kGaussNode : -kGaussNode, (gp & 1) ? kGaussNode : -kGaussNode, P);
-    TC val[5], grad[5][3];
+    TC val[5], grad[5][3], ih;
     const bool fb = (mask[idx] >> bit) & 1u;
     if (fs_stride) {
       // the neighbour across face f and its reconstruction for that face
@@ -1578,16 +1544,16 @@ __global__ void __launch_bounds__(kBlock) k_debug_gp_hex(HexGrid H, const TC* __
       face_frame(Pc, fn, f1, f2);
       CharFrame B;
       char_frame(Qb, fn, f1, f2, gamma, B);
-      eval_char_hex(cv, geo, N, idx, zero, P.x, fb, B, val, grad);
+      eval_char_hex(cv, geo, N, idx, zero, P.x, fb, B, val, grad, ih);
     } else {
-      eval_hex(coef, geo, N, idx, zero, P.x, fb, val, grad);
+      eval_hex(coef, geo, N, idx, zero, P.x, fb, val, grad, ih);
     }
     for (int v = 0; v < 5; ++v) {
       double* o = out + ((idx * 24 + bit) * 5 + v) * 4;
       o[0] = val[v];
-      o[1] = grad[v][0];
-      o[2] = grad[v][1];
-      o[3] = grad[v][2];
+      o[1] = grad[v][0] * ih;
+      o[2] = grad[v][1] * ih;
+      o[3] = grad[v][2] * ih;
     }
   }
 }

@@ -423,7 +423,7 @@ hgks_status hex_stage(hgks_ctx c, const double* qin, double dt, double alpha) {
   const bool ext = c->cfg.prandtl != 1.0 || c->cfg.mu_exponent != 0.0;
   const TC* fc = (const TC*)c->coef() + (fs ? c->G.fs_stride : 0);
 #define HGKS_HEX_FLUX(E, F)                                                                                      \
-  hipLaunchKernelGGL((k_flux_hex<TC, E, F>), dim3(pad8(3 * nb)), dim3(kBlock), 0, c->stream, H, fc, c->geo(),    \
+  hipLaunchKernelGGL((k_flux_hex<TC, E, F>), dim3(pad8(3 * nb * kFluxSubs)), dim3(kFluxLanes), 0, c->stream, H, fc, c->geo(),    \
                      c->mask(), (TC*)c->face(0), (TC*)c->face(1), (TC*)c->face(2), c->vface(0), c->vface(1),     \
                      c->vface(2), gp, TC(dt), TC(1.0 / dt), N, nb)
   if (ext && fs)
