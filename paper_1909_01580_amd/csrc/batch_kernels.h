@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_recon(const BatchGrid<TC>* __r
     size_t idx;
     if (batch_cell(B[g], t - B[g].t_cell, threadIdx.x, idx))
       recon_box_cell<TC, WIDE, COEF>(q + B[g].q_off, coef + B[g].coef_off, mask + B[g].mask_off, B[g].G, B[g].P, margin,
-                               gm1, B[g].N, idx);
+                                     gm1, idx);
   });
 }
 

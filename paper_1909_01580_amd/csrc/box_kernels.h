@@ -18,6 +18,8 @@
 //             n_d + 1 (outflow), the other two extents n.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 #include "char_basis.h"
 #include "gks_flux.h"
@@ -358,102 +360,119 @@ HGKS_FN FaceLane wave_face(const BoxGrid& G, unsigned lb, unsigned first, unsign
 }
 
 // ---------------------------------------------------------------- recon
-// Reconstruction of reconstruction-box cell idx (< NR).  WIDE: the
-// stencils of Remark 1 (the big stencil reaches two cells along the axes);
-// COEF = false: the fallback mask only (the characteristic reconstruction
-// stores its own coefficients).
-template <typename TC, bool WIDE = false, bool COEF = true>
-__device__ __forceinline__ void recon_box_cell(const double* __restrict__ q, TC* __restrict__ coef,
-                                               uint32_t* __restrict__ mask, const BoxGrid& G,
-                                               const WenoParams<TC>& P, TC margin, TC gm1, size_t NR, size_t idx) {
+// Appends idx to the list of flagged cells for the active lanes with
+// `flagged` set: one counter add per wave.
+__device__ __forceinline__ void append_flagged(uint32_t* __restrict__ list, uint32_t* __restrict__ counter,
+                                               bool flagged, uint32_t idx) {
+  const uint64_t ballot = __ballot(flagged);
+  if (ballot == 0) return;
+  const int lane = (int)(threadIdx.x & 63u);
+  const int leader = __ffsll((long long)ballot) - 1;
+  uint32_t base = 0;
+  if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(ballot));
+  base = __shfl(base, leader);
+  if (flagged) {
+    const uint64_t below = lane ? (ballot & ((~0ull) >> (64 - lane))) : 0ull;
+    list[base + (uint32_t)__popcll(below)] = idx;
+  }
+}
+
+// Neighbourhood of a reconstruction-box cell: real indices (boundary rule
+// applied) and momentum signs (mirror images) of the neighbours one cell
+// away per axis, and with the wide stencil two cells away.
+template <bool WIDE>
+struct BoxNbr {
+  int ix[3], iy[3], iz[3];
+  double sx[3], sy[3], sz[3];
+  int fx[2], fy[2], fz[2];
+  double gx[2], gy[2], gz[2];
+};
+
+template <bool WIDE>
+__device__ __forceinline__ void box_nbr(const BoxGrid& G, size_t idx, BoxNbr<WIDE>& B) {
   int ri, rj, rk;
   split_index((uint32_t)idx, G.nr[0], G.nr[1], G.inv_nr[0], G.inv_nr[1], ri, rj, rk);
   const int i = ri - G.g[0], j = rj - G.g[1], k = rk - G.g[2];
-  int ix[3], iy[3], iz[3];
-  double sx[3], sy[3], sz[3];  // momentum signs of mirror images
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
-    ix[o] = bc_index(G, 0, i + o - 1, sx[o]);
-    iy[o] = bc_index(G, 1, j + o - 1, sy[o]);
-    iz[o] = bc_index(G, 2, k + o - 1, sz[o]);
+    B.ix[o] = bc_index(G, 0, i + o - 1, B.sx[o]);
+    B.iy[o] = bc_index(G, 1, j + o - 1, B.sy[o]);
+    B.iz[o] = bc_index(G, 2, k + o - 1, B.sz[o]);
   }
-  // cells two steps away along each axis (wide stencil only)
-  int fx[2] = {0, 0}, fy[2] = {0, 0}, fz[2] = {0, 0};
-  double gx[2] = {1.0, 1.0}, gy[2] = {1.0, 1.0}, gz[2] = {1.0, 1.0};
   if constexpr (WIDE) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      fx[t] = bc_index(G, 0, i + 4 * t - 2, gx[t]);
-      fy[t] = bc_index(G, 1, j + 4 * t - 2, gy[t]);
-      fz[t] = bc_index(G, 2, k + 4 * t - 2, gz[t]);
+      B.fx[t] = bc_index(G, 0, i + 4 * t - 2, B.gx[t]);
+      B.fy[t] = bc_index(G, 1, j + 4 * t - 2, B.gy[t]);
+      B.fz[t] = bc_index(G, 2, k + 4 * t - 2, B.gz[t]);
     }
   }
-  const size_t N = (size_t)G.n[0] * G.n[1] * G.n[2];
+}
+
+// Reconstruction of variable V of one cell: its mean and the polynomial
+// (with the bound over all polynomials and points).
+template <int V, typename TC, bool WIDE>
+__device__ __forceinline__ void recon_box_var(const double* __restrict__ q, const BoxGrid& G, const BoxNbr<WIDE>& B,
+                                              const WenoParams<TC>& P, double& c, BoxRecon<TC>& r) {
   // element offsets in 32 bits (fewer than 2^29 cells), byte offsets from
-  // each variable's uniform base
+  // the variable's uniform base
   const unsigned nx = (unsigned)G.n[0], nxy = (unsigned)G.n[0] * (unsigned)G.n[1];
-  TC qc[5], bnd[5];
+  const double* qv = q + (size_t)V * nxy * (unsigned)G.n[2];
+  auto ld = [&](int z, int y, int x) {
+    return *(const double*)((const char*)qv + ((unsigned)z * nxy + (unsigned)y * nx + (unsigned)x) * 8u);
+  };
+  // sign of variable V in the cell at offset o: the momentum component
+  // along an axis flips in a mirror image across that axis
+  auto sg = [&](int ox, int oy, int oz) -> double {
+    return V == 1 ? B.sx[ox + 1] : (V == 2 ? B.sy[oy + 1] : (V == 3 ? B.sz[oz + 1] : 1.0));
+  };
+  c = sg(0, 0, 0) * ld(B.iz[1], B.iy[1], B.ix[1]);
+  TC d[27];
 #pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    const double* qv = q + v * N;
-    auto ld = [&](int z, int y, int x) {
-      return *(const double*)((const char*)qv + ((unsigned)z * nxy + (unsigned)y * nx + (unsigned)x) * 8u);
-    };
-    // sign of variable v in the cell at offset o: the momentum component
-    // along an axis flips in a mirror image across that axis
-    auto sg = [&](int ox, int oy, int oz) -> double {
-      return v == 1 ? sx[ox + 1] : (v == 2 ? sy[oy + 1] : (v == 3 ? sz[oz + 1] : 1.0));
-    };
-    const double c = sg(0, 0, 0) * ld(iz[1], iy[1], ix[1]);
-    TC d[27];
+  for (int oz = -1; oz <= 1; ++oz)
 #pragma unroll
-    for (int oz = -1; oz <= 1; ++oz)
+    for (int oy = -1; oy <= 1; ++oy)
 #pragma unroll
-      for (int oy = -1; oy <= 1; ++oy)
-#pragma unroll
-        for (int ox = -1; ox <= 1; ++ox) {
-          const int nz = (ox != 0) + (oy != 0) + (oz != 0);
-          if (nz == 0 || nz == 3) {
-            d[sidx(ox, oy, oz)] = TC(0);
-          } else {
-            d[sidx(ox, oy, oz)] =
-                TC(sg(ox, oy, oz) * ld(iz[oz + 1], iy[oy + 1], ix[ox + 1]) - c);
-          }
+      for (int ox = -1; ox <= 1; ++ox) {
+        const int nz = (ox != 0) + (oy != 0) + (oz != 0);
+        if (nz == 0 || nz == 3) {
+          d[sidx(ox, oy, oz)] = TC(0);
+        } else {
+          d[sidx(ox, oy, oz)] = TC(sg(ox, oy, oz) * ld(B.iz[oz + 1], B.iy[oy + 1], B.ix[ox + 1]) - c);
         }
-    BoxRecon<TC> r;
-    if constexpr (WIDE) {
-      // far cells: (-2x, +2x, -2y, +2y, -2z, +2z); a mirror flips the
-      // momentum along its own axis
-      TC f[6];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const double s0 = v == 1 ? gx[t] : (v == 2 ? sy[1] : (v == 3 ? sz[1] : 1.0));
-        const double s1 = v == 1 ? sx[1] : (v == 2 ? gy[t] : (v == 3 ? sz[1] : 1.0));
-        const double s2 = v == 1 ? sx[1] : (v == 2 ? sy[1] : (v == 3 ? gz[t] : 1.0));
-        f[t] = TC(s0 * ld(iz[1], iy[1], fx[t]) - c);
-        f[2 + t] = TC(s1 * ld(iz[1], fy[t], ix[1]) - c);
-        f[4 + t] = TC(s2 * ld(fz[t], iy[1], ix[1]) - c);
       }
-      weno_box_wide(d, f, P, r);
-    } else {
-      weno_box(d, P, r);
-    }
-    if constexpr (COEF) {
-      TC* cv = coef + coef_cell<TC>(idx) + v * 10 * kCB<TC>;
-      cv[0] = TC(c);
+  if constexpr (WIDE) {
+    // far cells: (-2x, +2x, -2y, +2y, -2z, +2z); a mirror flips the
+    // momentum along its own axis
+    TC f[6];
 #pragma unroll
-      for (int m = 0; m < 9; ++m) cv[(m + 1) * kCB<TC>] = r.c[m];
+    for (int t = 0; t < 2; ++t) {
+      const double s0 = V == 1 ? B.gx[t] : (V == 2 ? B.sy[1] : (V == 3 ? B.sz[1] : 1.0));
+      const double s1 = V == 1 ? B.sx[1] : (V == 2 ? B.gy[t] : (V == 3 ? B.sz[1] : 1.0));
+      const double s2 = V == 1 ? B.sx[1] : (V == 2 ? B.sy[1] : (V == 3 ? B.gz[t] : 1.0));
+      f[t] = TC(s0 * ld(B.iz[1], B.iy[1], B.fx[t]) - c);
+      f[2 + t] = TC(s1 * ld(B.iz[1], B.fy[t], B.ix[1]) - c);
+      f[4 + t] = TC(s2 * ld(B.fz[t], B.iy[1], B.ix[1]) - c);
     }
-    qc[v] = TC(c);
-    bnd[v] = r.bound;
-    // The next variable's stencil loads wait for this variable's results
-    // (an empty asm ties their indices to them), so the compiler does not
-    // hoist all five stencils ahead and hold them in registers at once.
-    asm volatile("" : "+v"(iz[0]), "+v"(iz[1]), "+v"(iz[2]) : "v"(r.c[0]), "v"(r.bound));
+    weno_box_wide(d, f, P, r);
+  } else {
+    weno_box(d, P, r);
   }
-  // Sufficient test that no polynomial can give rho <= 0 or p < 0 at a
-  // Gauss point: bounds of every variable over all 25 polynomials and 24
-  // points; the exact test runs only where this one fails.
+}
+
+template <typename TC>
+__device__ __forceinline__ void store_recon(TC* __restrict__ coef, size_t idx, int v, double c, const BoxRecon<TC>& r) {
+  TC* cv = coef + coef_cell<TC>(idx) + v * 10 * kCB<TC>;
+  cv[0] = TC(c);
+#pragma unroll
+  for (int m = 0; m < 9; ++m) cv[(m + 1) * kCB<TC>] = r.c[m];
+}
+
+// Sufficient test that no polynomial can give rho <= 0 or p < 0 at a Gauss
+// point, from the means qc and the bounds bnd of every variable over all 25
+// polynomials and 24 points; the exact test runs only where this one fails.
+template <typename TC>
+HGKS_FN bool surely_physical(const TC (&qc)[5], const TC (&bnd)[5], TC margin, TC gm1) {
   const TC rmin = qc[0] - bnd[0];
   bool safe = rmin > margin * qc[0];
   if (safe) {
@@ -466,134 +485,224 @@ __device__ __forceinline__ void recon_box_cell(const double* __restrict__ q, TC*
     const TC emin = qc[4] - bnd[4];
     safe = gm1 * (emin - TC(0.5) * msq * d_rcp(rmin)) > margin * gm1 * (d_abs(qc[4]) + bnd[4]);
   }
-  mask[idx] = safe ? 0u : kNeedsCheck;
+  return safe;
 }
 
+// Reconstruction of reconstruction-box cell idx (< NR); returns whether the
+// exact positivity test has to look at it.  WIDE: the stencils of Remark 1
+// (the big stencil reaches two cells along the axes); COEF = false: the
+// fallback mask only (the characteristic reconstruction stores its own
+// coefficients).
+template <typename TC, bool WIDE = false, bool COEF = true>
+__device__ __forceinline__ bool recon_box_cell(const double* __restrict__ q, TC* __restrict__ coef,
+                                               uint32_t* __restrict__ mask, const BoxGrid& G,
+                                               const WenoParams<TC>& P, TC margin, TC gm1, size_t idx) {
+  BoxNbr<WIDE> B;
+  box_nbr(G, idx, B);
+  TC qc[5], bnd[5];
+  auto var = [&](auto vc) {
+    constexpr int V = decltype(vc)::value;
+    double c;
+    BoxRecon<TC> r;
+    recon_box_var<V, TC, WIDE>(q, G, B, P, c, r);
+    if constexpr (COEF) store_recon(coef, idx, V, c, r);
+    qc[V] = TC(c);
+    bnd[V] = r.bound;
+    // The next variable's stencil loads wait for this variable's results
+    // (an empty asm ties their indices to them), so the compiler does not
+    // hoist all five stencils ahead and hold them in registers at once.
+    asm volatile("" : "+v"(B.iz[0]), "+v"(B.iz[1]), "+v"(B.iz[2]) : "v"(r.c[0]), "v"(r.bound));
+  };
+  var(std::integral_constant<int, 0>());
+  var(std::integral_constant<int, 1>());
+  var(std::integral_constant<int, 2>());
+  var(std::integral_constant<int, 3>());
+  var(std::integral_constant<int, 4>());
+  const bool check = !surely_physical(qc, bnd, margin, gm1);
+  mask[idx] = check ? kNeedsCheck : 0u;
+  return check;
+}
+
+// One lane per cell; flagged cells go to the list (counter zero before).
 template <typename TC, bool WIDE = false, bool COEF = true>
 __global__ void __launch_bounds__(kBlock) k_recon_box(const double* __restrict__ q, TC* __restrict__ coef,
                                                       uint32_t* __restrict__ mask, BoxGrid G,
                                                       WenoParams<TC> P, TC margin, TC gm1, size_t NR,
-                                                      unsigned nblk) {
+                                                      unsigned nblk, uint32_t* __restrict__ list,
+                                                      uint32_t* __restrict__ counter) {
   const unsigned b = xcd_block(blockIdx.x, gridDim.x);
   if (b >= nblk) return;
   const size_t idx = (size_t)b * kBlock + threadIdx.x;
   if (idx >= NR) return;
-  recon_box_cell<TC, WIDE, COEF>(q, coef, mask, G, P, margin, gm1, NR, idx);
+  const bool check = recon_box_cell<TC, WIDE, COEF>(q, coef, mask, G, P, margin, gm1, idx);
+  append_flagged(list, counter, check, (uint32_t)idx);
+}
+
+// The same with one wave per variable of 64 cells (a workgroup of five
+// waves): a small grid has too few cells to fill the chip, and the five
+// variables of a lane follow one another.  The means and bounds meet in LDS
+// for the positivity pre-test.
+constexpr int kSplitCells = 64, kSplitLanes = 5 * kSplitCells;
+
+template <typename TC, bool WIDE = false, bool COEF = true>
+__global__ void __launch_bounds__(kSplitLanes) k_recon_box_split(const double* __restrict__ q, TC* __restrict__ coef,
+                                                                 uint32_t* __restrict__ mask, BoxGrid G,
+                                                                 WenoParams<TC> P, TC margin, TC gm1, size_t NR,
+                                                                 unsigned nblk, uint32_t* __restrict__ list,
+                                                                 uint32_t* __restrict__ counter) {
+  __shared__ TC sq[5][kSplitCells], sb[5][kSplitCells];
+  const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+  if (b >= nblk) return;
+  const int lane = (int)(threadIdx.x & 63u);
+  const int v = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const size_t idx = (size_t)b * kSplitCells + (size_t)lane;
+  if (idx < NR) {
+    BoxNbr<WIDE> B;
+    box_nbr(G, idx, B);
+    auto var = [&](auto vc) {
+      constexpr int V = decltype(vc)::value;
+      double c;
+      BoxRecon<TC> r;
+      recon_box_var<V, TC, WIDE>(q, G, B, P, c, r);
+      if constexpr (COEF) store_recon(coef, idx, V, c, r);
+      sq[V][lane] = TC(c);
+      sb[V][lane] = r.bound;
+    };
+    switch (v) {
+      case 0: var(std::integral_constant<int, 0>()); break;
+      case 1: var(std::integral_constant<int, 1>()); break;
+      case 2: var(std::integral_constant<int, 2>()); break;
+      case 3: var(std::integral_constant<int, 3>()); break;
+      default: var(std::integral_constant<int, 4>()); break;
+    }
+  }
+  __syncthreads();
+  if (v != 0 || idx >= NR) return;
+  TC qc[5], bnd[5];
+#pragma unroll
+  for (int e = 0; e < 5; ++e) {
+    qc[e] = sq[e][lane];
+    bnd[e] = sb[e][lane];
+  }
+  const bool check = !surely_physical(qc, bnd, margin, gm1);
+  mask[idx] = check ? kNeedsCheck : 0u;
+  append_flagged(list, counter, check, (uint32_t)idx);
 }
 
 // Exact fallback test (Sec. 4): for every Gauss point of the cell, any of
 // the 25 polynomials (9 with the stencils of Remark 1) with rho <= 0 or
-// p < 0 marks the point.  poly_bits: the 24 point bits of polynomial m
-// (m = 0 the big stencil's, then the sub-stencils') of a cell whose
-// stencil values at(v, ox, oy, oz) (variable v of the cell at that offset,
-// boundary images and mirror signs applied) the accessor gives.
+// p < 0 marks the point.
+//
+// Unit-cube coordinates of Gauss point gp of face f: the face axis d takes
+// +-1/2, axes d+1 and d+2 (cyclic) the Gauss nodes.
+template <typename TC>
+HGKS_FN void pos_gauss(int f, int gp, TC (&x)[3]) {
+  const int d = f >> 1;
+  const TC xs = (f & 1) ? TC(0.5) : TC(-0.5);
+  const TC pa = (gp >> 1) ? TC(kGaussNode) : TC(-kGaussNode);
+  const TC pb = (gp & 1) ? TC(kGaussNode) : TC(-kGaussNode);
+  x[0] = d == 0 ? xs : (d == 2 ? pa : pb);
+  x[1] = d == 1 ? xs : (d == 0 ? pa : pb);
+  x[2] = d == 2 ? xs : (d == 1 ? pa : pb);
+}
+
+// P_0 of one variable whose stencil values at(ox, oy, oz) (boundary images
+// and mirror signs applied) the accessor gives.
+template <typename TC, bool WIDE, typename AT>
+__device__ __forceinline__ void pos_quadratic(const AT& at, TC (&cf)[9]) {
+  const double c = at(0, 0, 0);
+  TC d[27];
+#pragma unroll
+  for (int oz = -1; oz <= 1; ++oz)
+#pragma unroll
+    for (int oy = -1; oy <= 1; ++oy)
+#pragma unroll
+      for (int ox = -1; ox <= 1; ++ox) {
+        const int nz = (ox != 0) + (oy != 0) + (oz != 0);
+        d[sidx(ox, oy, oz)] = (nz == 0 || nz == 3) ? TC(0) : TC(at(ox, oy, oz) - c);
+      }
+  if constexpr (WIDE) {
+    const TC f[6] = {TC(at(-2, 0, 0) - c), TC(at(2, 0, 0) - c), TC(at(0, -2, 0) - c),
+                     TC(at(0, 2, 0) - c), TC(at(0, 0, -2) - c), TC(at(0, 0, 2) - c)};
+    big_quadratic_wide(d, f, cf);
+  } else {
+    big_quadratic(d, cf);
+  }
+}
+
+// Slopes of sub-stencil ms of one variable.
+template <typename TC, bool WIDE, typename AT>
+__device__ __forceinline__ void pos_linear(const AT& at, int ms, TC (&b)[3]) {
+  const double c = at(0, 0, 0);
+  if constexpr (WIDE) {
+    const int sx = (ms & 1) ? -1 : 1, sy = (ms & 2) ? -1 : 1, sz = (ms & 4) ? -1 : 1;
+    b[0] = TC(sx) * TC(at(sx, 0, 0) - c);
+    b[1] = TC(sy) * TC(at(0, sy, 0) - c);
+    b[2] = TC(sz) * TC(at(0, 0, sz) - c);
+  } else {
+    const int t = ms / 8, r = ms % 8;
+    const int sa = (r & 1) ? -1 : 1, sb = (r & 2) ? -1 : 1, sc = (r & 4) ? -1 : 1;
+    // axis triple (a, b; c) = (t, t+1; t+2) cyclic; offsets as (x, y, z)
+    const int ea = t, eb = t == 2 ? 0 : t + 1, ec = t == 0 ? 2 : t - 1;
+    const int oa[3] = {ea == 0 ? sa : 0, ea == 1 ? sa : 0, ea == 2 ? sa : 0};
+    const int ob[3] = {eb == 0 ? sb : 0, eb == 1 ? sb : 0, eb == 2 ? sb : 0};
+    const int oc[3] = {ec == 0 ? sc : 0, ec == 1 ? sc : 0, ec == 2 ? sc : 0};
+    const TC da = TC(at(oa[0], oa[1], oa[2]) - c);
+    const TC db = TC(at(ob[0], ob[1], ob[2]) - c);
+    const TC dab = TC(at(oa[0] + ob[0], oa[1] + ob[1], oa[2] + ob[2]) - c);
+    const TC dc = TC(at(oc[0], oc[1], oc[2]) - c);
+    const TC ba = TC(sa) * (TC(2) * da - db + dab) * TC(1.0 / 3.0);
+    const TC bb = TC(sb) * (TC(2) * db - da + dab) * TC(1.0 / 3.0);
+    const TC bc = TC(sc) * dc;
+    // slope along x, y, z by selects
+    b[0] = ea == 0 ? ba : (eb == 0 ? bb : bc);
+    b[1] = ea == 1 ? ba : (eb == 1 ? bb : bc);
+    b[2] = ea == 2 ? ba : (eb == 2 ? bb : bc);
+  }
+}
+
+// rho <= 0 or p < 0 of the values val.
+template <typename TC>
+HGKS_FN bool not_physical(const TC (&val)[5], TC gm1) {
+  if (!(val[0] > TC(0))) return true;
+  return gm1 * (val[4] - TC(0.5) * (val[1] * val[1] + val[2] * val[2] + val[3] * val[3]) / val[0]) < TC(0);
+}
+
+// poly_bits: the 24 point bits of polynomial m (m = 0 the big stencil's,
+// then the sub-stencils') of a cell with stencil values at(v, ox, oy, oz).
 template <typename TC, bool WIDE, typename AT>
 __device__ __forceinline__ uint32_t poly_bits(const AT& at, TC gm1, int m) {
-  TC qc[5];
+  TC cf[5][9];
 #pragma unroll
-  for (int v = 0; v < 5; ++v) qc[v] = TC(at(v, 0, 0, 0));
-  // Values at the 24 points of one polynomial per variable (coefficients in
-  // registers, indices fixed after unrolling), then the test.
-  auto test = [&](const TC (&cf)[5][9]) -> uint32_t {
-    uint32_t bits = 0;
+  for (int v = 0; v < 5; ++v) {
+    auto one = [&](int ox, int oy, int oz) -> double { return at(v, ox, oy, oz); };
+    if (m == 0) {
+      pos_quadratic<TC, WIDE>(one, cf[v]);
+    } else {
+      TC b[3];
+      pos_linear<TC, WIDE>(one, m - 1, b);
+#pragma unroll
+      for (int t = 0; t < 9; ++t) cf[v][t] = t < 3 ? b[t] : TC(0);
+    }
+    // one variable's stencil in registers at a time
+    asm volatile("" ::: "memory");
+  }
+  uint32_t bits = 0;
 #pragma unroll 1
-    for (int f = 0; f < 6; ++f) {
-      const int d = f >> 1;
-      const TC xs = (f & 1) ? TC(0.5) : TC(-0.5);
+  for (int f = 0; f < 6; ++f) {
 #pragma unroll
-      for (int gp = 0; gp < 4; ++gp) {
-      const int bit = 4 * f + gp;
-      // the face axis d takes xs, axes d+1 and d+2 (cyclic) the Gauss nodes
-      const TC pa = (gp >> 1) ? TC(kGaussNode) : TC(-kGaussNode);
-      const TC pb = (gp & 1) ? TC(kGaussNode) : TC(-kGaussNode);
-      const TC x0 = d == 0 ? xs : (d == 2 ? pa : pb);
-      const TC x1 = d == 1 ? xs : (d == 0 ? pa : pb);
-      const TC x2 = d == 2 ? xs : (d == 1 ? pa : pb);
-      TC val[5];
+    for (int gp = 0; gp < 4; ++gp) {
+      TC x[3], val[5];
+      pos_gauss<TC>(f, gp, x);
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         TC gx, gy, gz;
-        quad_eval(qc[v], cf[v], x0, x1, x2, val[v], gx, gy, gz);
+        quad_eval(TC(at(v, 0, 0, 0)), cf[v], x[0], x[1], x[2], val[v], gx, gy, gz);
       }
-      bool bad = !(val[0] > TC(0));
-      if (!bad) {
-        const TC p = gm1 * (val[4] - TC(0.5) * (val[1] * val[1] + val[2] * val[2] + val[3] * val[3]) / val[0]);
-        bad = p < TC(0);
-      }
-      if (bad) bits |= 1u << bit;
-      }
+      if (not_physical(val, gm1)) bits |= 1u << (4 * f + gp);
     }
-    return bits;
-  };
-  if (m == 0) {
-    // P_0 from the big stencil
-    TC cf[5][9];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      const double c = at(v, 0, 0, 0);
-      TC d[27];
-#pragma unroll
-      for (int oz = -1; oz <= 1; ++oz)
-#pragma unroll
-        for (int oy = -1; oy <= 1; ++oy)
-#pragma unroll
-          for (int ox = -1; ox <= 1; ++ox) {
-            const int nz = (ox != 0) + (oy != 0) + (oz != 0);
-            d[sidx(ox, oy, oz)] = (nz == 0 || nz == 3) ? TC(0) : TC(at(v, ox, oy, oz) - c);
-          }
-      if constexpr (WIDE) {
-        const TC f[6] = {TC(at(v, -2, 0, 0) - c), TC(at(v, 2, 0, 0) - c), TC(at(v, 0, -2, 0) - c),
-                         TC(at(v, 0, 2, 0) - c), TC(at(v, 0, 0, -2) - c), TC(at(v, 0, 0, 2) - c)};
-        big_quadratic_wide(d, f, cf[v]);
-      } else {
-        big_quadratic(d, cf[v]);
-      }
-      // one variable's stencil in registers at a time
-      asm volatile("" ::: "memory");
-    }
-    return test(cf);
   }
-  {
-    // linear sub-stencil polynomial m - 1
-    const int ms = m - 1;
-    TC cf[5][9];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      const double c = at(v, 0, 0, 0);
-#pragma unroll
-      for (int t = 3; t < 9; ++t) cf[v][t] = TC(0);
-      TC b[3];
-      if constexpr (WIDE) {
-        const int sx = (ms & 1) ? -1 : 1, sy = (ms & 2) ? -1 : 1, sz = (ms & 4) ? -1 : 1;
-        b[0] = TC(sx) * TC(at(v, sx, 0, 0) - c);
-        b[1] = TC(sy) * TC(at(v, 0, sy, 0) - c);
-        b[2] = TC(sz) * TC(at(v, 0, 0, sz) - c);
-      } else {
-        const int t = ms / 8, r = ms % 8;
-        const int sa = (r & 1) ? -1 : 1, sb = (r & 2) ? -1 : 1, sc = (r & 4) ? -1 : 1;
-        // axis triple (a, b; c) = (t, t+1; t+2) cyclic; offsets as (x, y, z)
-        const int ea = t, eb = t == 2 ? 0 : t + 1, ec = t == 0 ? 2 : t - 1;
-        const int oa[3] = {ea == 0 ? sa : 0, ea == 1 ? sa : 0, ea == 2 ? sa : 0};
-        const int ob[3] = {eb == 0 ? sb : 0, eb == 1 ? sb : 0, eb == 2 ? sb : 0};
-        const int oc[3] = {ec == 0 ? sc : 0, ec == 1 ? sc : 0, ec == 2 ? sc : 0};
-        const TC da = TC(at(v, oa[0], oa[1], oa[2]) - c);
-        const TC db = TC(at(v, ob[0], ob[1], ob[2]) - c);
-        const TC dab = TC(at(v, oa[0] + ob[0], oa[1] + ob[1], oa[2] + ob[2]) - c);
-        const TC dc = TC(at(v, oc[0], oc[1], oc[2]) - c);
-        const TC ba = TC(sa) * (TC(2) * da - db + dab) * TC(1.0 / 3.0);
-        const TC bb = TC(sb) * (TC(2) * db - da + dab) * TC(1.0 / 3.0);
-        const TC bc = TC(sc) * dc;
-        // slope along x, y, z by selects (the axis of each is uniform)
-        b[0] = ea == 0 ? ba : (eb == 0 ? bb : bc);
-        b[1] = ea == 1 ? ba : (eb == 1 ? bb : bc);
-        b[2] = ea == 2 ? ba : (eb == 2 ? bb : bc);
-      }
-      cf[v][0] = b[0];
-      cf[v][1] = b[1];
-      cf[v][2] = b[2];
-    }
-    return test(cf);
-  }
+  return bits;
 }
 
 // poly_bits of reconstruction-box cell idx, its stencil read from the state.
@@ -624,26 +733,6 @@ __device__ __forceinline__ void posit_exact_box_cell(const double* __restrict__ 
   mask[idx] = bits;
 }
 
-// The exact test runs on a list of the flagged cells: k_posit_compact
-// appends them (one counter add per wave), then k_posit_group_box tests each
-// listed cell.  counter[0] must be zero before k_posit_compact.
-__global__ void __launch_bounds__(kBlock) k_posit_compact(const uint32_t* __restrict__ mask, size_t NR,
-                                                          uint32_t* __restrict__ list, uint32_t* __restrict__ counter) {
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool flagged = idx < NR && (mask[idx] & kNeedsCheck);
-  const uint64_t ballot = __ballot(flagged);
-  if (ballot == 0) return;
-  const int lane = (int)(threadIdx.x & 63u);
-  const int leader = __ffsll((long long)ballot) - 1;
-  uint32_t base = 0;
-  if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(ballot));
-  base = __shfl(base, leader);
-  if (flagged) {
-    const uint64_t below = lane ? (ballot & ((~0ull) >> (64 - lane))) : 0ull;
-    list[base + (uint32_t)__popcll(below)] = (uint32_t)idx;
-  }
-}
-
 // Stencil points of the exact test: the 27 cells of the 3x3x3 block, then
 // (Remark 1 only) the six cells two steps away along the axes.
 template <bool WIDE>
@@ -669,13 +758,20 @@ HGKS_FN int pos_slot(int ox, int oy, int oz) {
   return 27 + 2 * a + (s > 0 ? 1 : 0);
 }
 
-// The exact test on the list of flagged cells, one 32-lane group per cell:
-// the group stages the cell's stencil (boundary images and mirror signs
-// applied) in LDS once, then lane m tests polynomial m; the lanes' point
-// bits are or-ed across the group and written as the cell's mask word,
-// which also clears its "needs the test" bit.  The pass loop is uniform
-// over the workgroup (its bound depends on the block only), so the
-// barriers are reached by every lane.
+// The exact test on the list of flagged cells, one 32-lane group per cell.
+// The group stages the cell's stencil (boundary images and mirror signs
+// applied) in LDS once.  Then lane p < 24 tests the quadratic P_0 at point
+// p -- its coefficients formed by five lanes, one variable each -- and the
+// linear polynomials at all points: with 24 sub-stencils one each, with the
+// eight of Remark 1 a third of one's points each (the two faces of an
+// axis).  The lanes' point bits are or-ed across the group and written as
+// the cell's mask word, which also clears its "needs the test" bit.  (One
+// lane per polynomial left P_0's lane to walk 24 quadratic points alone
+// while the others waited: 70 us per stage against 16 us on the 97x50x35
+// blast with the stencils of Remark 1, 28 against 7.7 us on the 40^3 Sedov
+// octant.)  The pass loop is uniform over the
+// workgroup (its bound depends on the block only), so the barriers are
+// reached by every lane.
 constexpr int kPosGroups = kBlock / 32;
 
 template <typename TC, bool WIDE = false>
@@ -685,6 +781,7 @@ __global__ void __launch_bounds__(kBlock) k_posit_group_box(const double* __rest
                                                             const uint32_t* __restrict__ counter) {
   constexpr int NP = kPosPoints<WIDE>;
   __shared__ double st[kPosGroups][5][NP];
+  __shared__ TC big[kPosGroups][5][9];
   const uint32_t count = counter[0];
   const int grp = (int)(threadIdx.x >> 5), lane = (int)(threadIdx.x & 31u);
   const size_t nx = G.n[0], nxy = (size_t)G.n[0] * G.n[1], N = nxy * G.n[2];
@@ -709,10 +806,49 @@ __global__ void __launch_bounds__(kBlock) k_posit_group_box(const double* __rest
       }
     }
     __syncthreads();
+    auto at = [&](int v, int ox, int oy, int oz) -> double { return st[grp][v][pos_slot(ox, oy, oz)]; };
+    if (lane >= 27) {
+      const int v = lane - 27;
+      auto one = [&](int ox, int oy, int oz) -> double { return at(v, ox, oy, oz); };
+      TC cf[9];
+      pos_quadratic<TC, WIDE>(one, cf);
+#pragma unroll
+      for (int m = 0; m < 9; ++m) big[grp][v][m] = cf[m];
+    }
+    __syncthreads();
     uint32_t bits = 0;
-    if (live && lane < kPosPolys<WIDE>) {
-      auto at = [&](int v, int ox, int oy, int oz) -> double { return st[grp][v][pos_slot(ox, oy, oz)]; };
-      bits = poly_bits<TC, WIDE>(at, gm1, lane);
+    if (live && lane < 24) {
+      TC val[5];
+      {
+        TC x[3];
+        pos_gauss<TC>(lane >> 2, lane & 3, x);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          TC cf[9], gx, gy, gz;
+#pragma unroll
+          for (int m = 0; m < 9; ++m) cf[m] = big[grp][v][m];
+          quad_eval(TC(at(v, 0, 0, 0)), cf, x[0], x[1], x[2], val[v], gx, gy, gz);
+        }
+        if (not_physical(val, gm1)) bits |= 1u << lane;
+      }
+      TC qc[5], b[5][3];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        auto one = [&](int ox, int oy, int oz) -> double { return at(v, ox, oy, oz); };
+        qc[v] = TC(at(v, 0, 0, 0));
+        pos_linear<TC, WIDE>(one, WIDE ? lane & 7 : lane, b[v]);
+      }
+      const int f0 = WIDE ? (lane >> 3) * 2 : 0, f1 = WIDE ? f0 + 2 : 6;
+      for (int f = f0; f < f1; ++f) {
+#pragma unroll
+        for (int gp = 0; gp < 4; ++gp) {
+          TC x[3];
+          pos_gauss<TC>(f, gp, x);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) val[v] = qc[v] + b[v][0] * x[0] + b[v][1] * x[1] + b[v][2] * x[2];
+          if (not_physical(val, gm1)) bits |= 1u << (4 * f + gp);
+        }
+      }
     }
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) bits |= __shfl_xor(bits, o);
@@ -1132,8 +1268,10 @@ template <typename TF>
 __global__ void __launch_bounds__(kBlock) k_update_box(double* __restrict__ q, double* __restrict__ qs,
                                                        double* __restrict__ acc, const TF* __restrict__ fx,
                                                        const TF* __restrict__ fy, const TF* __restrict__ fz,
-                                                       BoxGrid G, double dt, int mode, size_t N) {
+                                                       BoxGrid G, double dt, int mode, size_t N,
+                                                       uint32_t* __restrict__ counter) {
   const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  if (idx == 0) *counter = 0u;  // empties the list of flagged cells for the next stage
   if (idx >= N) return;
   update_box_cell(q, qs, acc, fx, fy, fz, G, dt, mode, N, idx);
 }

@@ -270,7 +270,24 @@ TC* face_coef(hgks_ctx c) {
   return c->cfg.characteristic ? coef + c->G.fs_stride : coef;
 }
 
+// Cells of the reconstruction box up to which the reconstruction splits a
+// cell's variables over waves: up to about 40,000 cells the five waves per
+// 64 cells are resident at once (three per SIMD).  One launch, split against
+// one lane per cell, FP64: 16^3 6.8 against 13.9 us, 33x20x17 7 against
+// 14.7 us, but 42^3 (two rounds of waves either way, and each wave finds its
+// neighbours itself) 25 against 21.5 us.
+constexpr size_t kSplitMax = 40000;
+
+// Empties the list of flagged cells: before the first stage, and after a
+// stage that no update follows (the update does it otherwise).
+hgks_status reset_list(hgks_ctx c) {
+  if (c->cfg.moving) return HGKS_OK;
+  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, c->stream, c->plist() + c->D.NR);
+  return launched(c, "list reset");
+}
+
 // Reconstruction (with the fallback mask) and face fluxes of the state qin.
+// The list of flagged cells is empty before it.
 template <typename TC>
 hgks_status box_stage(hgks_ctx c, const double* qin, double dt) {
   const Dims& D = c->D;
@@ -280,26 +297,25 @@ hgks_status box_stage(hgks_ctx c, const double* qin, double dt) {
   const TC margin = sizeof(TC) == 8 ? TC(1e-10) : TC(1e-5);
   TC* coef = (TC*)c->coef();
   {
-    const unsigned nb = blocks_for(D.NR);
+    // Few cells: one wave per variable of 64 cells (kSplitCells), else one
+    // lane per cell.
+    const bool split = D.NR <= kSplitMax;
+    const unsigned nb = split ? (unsigned)((D.NR + kSplitCells - 1) / kSplitCells) : blocks_for(D.NR);
+    const unsigned lanes = split ? kSplitLanes : kBlock;
+    uint32_t* counter = c->plist() + D.NR;
     prof_mark(c, HGKS_PHASE_RECON, true);
-    if (c->cfg.stencil)
-      hipLaunchKernelGGL((k_recon_box<TC, true>), dim3(pad8(nb)), dim3(kBlock), 0, c->stream, qin, coef, c->mask(),
-                         c->G, P, margin, TC(c->cfg.gamma - 1.0), D.NR, nb);
-    else if (c->cfg.characteristic)  // the fallback mask only
-      hipLaunchKernelGGL((k_recon_box<TC, false, false>), dim3(pad8(nb)), dim3(kBlock), 0, c->stream, qin, coef,
-                         c->mask(), c->G, P, margin, TC(c->cfg.gamma - 1.0), D.NR, nb);
-    else
-      hipLaunchKernelGGL((k_recon_box<TC, false>), dim3(pad8(nb)), dim3(kBlock), 0, c->stream, qin, coef, c->mask(),
-                         c->G, P, margin, TC(c->cfg.gamma - 1.0), D.NR, nb);
+    auto recon = c->cfg.stencil ? (split ? k_recon_box_split<TC, true> : k_recon_box<TC, true>)
+                 : c->cfg.characteristic  // the fallback mask only
+                     ? (split ? k_recon_box_split<TC, false, false> : k_recon_box<TC, false, false>)
+                     : (split ? k_recon_box_split<TC> : k_recon_box<TC>);
+    hipLaunchKernelGGL(recon, dim3(pad8(nb)), dim3(lanes), 0, c->stream, qin, coef, c->mask(), c->G, P, margin,
+                       TC(c->cfg.gamma - 1.0), D.NR, nb, c->plist(), counter);
     prof_mark(c, HGKS_PHASE_RECON, false);
     if (hgks_status s = launched(c, "recon")) return s;
     prof_mark(c, HGKS_PHASE_FALLBACK, true);
-    // flagged cells to a list, then one 32-lane group per listed cell on a
-    // fixed grid of 8 workgroups per compute unit
-    uint32_t* counter = c->plist() + D.NR;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, c->stream, counter);
-    hipLaunchKernelGGL(k_posit_compact, dim3(nb), dim3(kBlock), 0, c->stream, c->mask(), D.NR, c->plist(), counter);
-    const unsigned pg = 2048;
+    // one 32-lane group per listed cell, on at most 8 workgroups per
+    // compute unit
+    const unsigned pg = (unsigned)std::min<size_t>(2048, (D.NR + kPosGroups - 1) / kPosGroups);
     if (c->cfg.stencil)
       hipLaunchKernelGGL((k_posit_group_box<TC, true>), dim3(pg), dim3(kBlock), 0, c->stream, qin, c->mask(), c->G,
                          TC(c->cfg.gamma - 1.0), c->plist(), counter);
@@ -342,12 +358,18 @@ hgks_status box_stage(hgks_ctx c, const double* qin, double dt) {
   return launched(c, "flux");
 }
 
+// A stage of the current state that no update follows (parity hooks).
+hgks_status box_only_stage(hgks_ctx c, double dt) {
+  if (hgks_status s = c->mixed() ? box_stage<float>(c, c->q(), dt) : box_stage<double>(c, c->q(), dt)) return s;
+  return reset_list(c);
+}
+
 template <typename TF>
 hgks_status box_update(hgks_ctx c, double dt, int mode) {
   prof_mark(c, HGKS_PHASE_UPDATE, true);
   hipLaunchKernelGGL((k_update_box<TF>), dim3(blocks_for(c->D.N)), dim3(kBlock), 0, c->stream, c->q(), c->qs(),
                      c->acc(), (const TF*)c->face(0), (const TF*)c->face(1), (const TF*)c->face(2), c->G, dt, mode,
-                     c->D.N);
+                     c->D.N, c->plist() + c->D.NR);
   prof_mark(c, HGKS_PHASE_UPDATE, false);
   return launched(c, "update");
 }
@@ -658,6 +680,7 @@ hgks_status hgks_set_state(hgks_ctx c, const double* q_dev) {
                                                   hipMemcpyDeviceToDevice, c->stream),
                                 "copy state"))
     return s;
+  if (hgks_status s = reset_list(c)) return s;
   c->state_set = true;
   return HGKS_OK;
 }
@@ -797,7 +820,7 @@ hgks_status hgks_debug_fallback_mask(hgks_ctx c, double dt, uint32_t* mask_dev_o
   if (c->cfg.moving)
     s = c->mixed() ? hex_stage<float>(c, c->q(), dt, 0.0) : hex_stage<double>(c, c->q(), dt, 0.0);
   else
-    s = c->mixed() ? box_stage<float>(c, c->q(), dt) : box_stage<double>(c, c->q(), dt);
+    s = box_only_stage(c, dt);
   if (s) return s;
   hipLaunchKernelGGL(k_debug_mask, dim3(blocks_for(c->D.N)), dim3(kBlock), 0, c->stream, c->mask(), c->G,
                      c->cfg.moving ? 0 : 1, c->D.N, mask_dev_out);
@@ -808,7 +831,7 @@ hgks_status hgks_debug_gp_states(hgks_ctx c, double dt, double* out) {
   if (hgks_status s = ready(c)) return s;
   if (!out || !(dt > 0.0)) return fail(HGKS_EINVAL, "bad arguments");
   if (c->cfg.moving) return hex_debug_gp(c, dt, out);
-  hgks_status s = c->mixed() ? box_stage<float>(c, c->q(), dt) : box_stage<double>(c, c->q(), dt);
+  hgks_status s = box_only_stage(c, dt);
   if (s) return s;
   if (c->mixed())
     hipLaunchKernelGGL((k_debug_gp_box<float>), dim3(blocks_for(c->D.N)), dim3(kBlock), 0, c->stream,
@@ -823,7 +846,7 @@ hgks_status hgks_debug_face_flux(hgks_ctx c, double dt, double* out) {
   if (hgks_status s = ready(c)) return s;
   if (!out || !(dt > 0.0)) return fail(HGKS_EINVAL, "bad arguments");
   if (c->cfg.moving) return hex_debug_face(c, dt, out);
-  hgks_status s = c->mixed() ? box_stage<float>(c, c->q(), dt) : box_stage<double>(c, c->q(), dt);
+  hgks_status s = box_only_stage(c, dt);
   if (s) return s;
   for (int d = 0; d < 3; ++d) {
     if (c->mixed())
@@ -944,6 +967,7 @@ hgks_status hgks_step_noalloc(const hgks_config* cfg, const double origin[3], co
                                 "copy state in"))
     return s;
   c->state_set = true;
+  if (hgks_status s = reset_list(c)) return s;
   if (hgks_status s = c->mixed() ? box_step<float>(c, dt, n_stages) : box_step<double>(c, dt, n_stages)) return s;
   return check_hip(c, hipMemcpyAsync(q_dev, c->q(), bytes, hipMemcpyDeviceToDevice, c->stream), "copy state out");
 }
