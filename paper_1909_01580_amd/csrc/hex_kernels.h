@@ -360,25 +360,29 @@ struct NbrGlobal {
   }
 };
 
-// LDS tile of the reconstruction: a kTX x kTY x kTZ block of cells and one
-// layer around it; per cell the centroid of its periodic image (shift
-// included), the central second moments and the five variables.
-constexpr int kTX = 8, kTY = 8, kTZ = 4;
-constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2, kHalo = kHX * kHY * kHZ;
-
-struct HexTile {
-  double c[3][kHalo];
-  double m[6][kHalo];
-  double q[5][kHalo];
+// LDS tile of a reconstruction: a block of TX x TY x TZ cells and one layer
+// around it; per cell the centroid of its periodic image (shift included),
+// the central second moments and the five variables.
+template <int TX_, int TY_, int TZ_>
+struct HexTileOf {
+  static constexpr int TX = TX_, TY = TY_, TZ = TZ_, HX = TX + 2, HY = TY + 2, HZ = TZ + 2, HALO = HX * HY * HZ;
+  double c[3][HALO];
+  double m[6][HALO];
+  double q[5][HALO];
 };
 
+// Tile of the component-wise reconstruction.
+constexpr int kTX = 8, kTY = 8, kTZ = 4;
+using HexTile = HexTileOf<kTX, kTY, kTZ>;
+
+template <typename TILE>
 struct NbrTile {
-  const HexTile& T;
+  const TILE& T;
   int base;  // tile index of the cell itself
   template <bool MOM>
   __device__ __forceinline__ void get(int ox, int oy, int oz, const HexCell& Ci, const double (&qc)[5],
                                       double (&d)[3], double (&mo)[6], double (&dq)[5]) const {
-    const int s = base + (oz * kHY + oy) * kHX + ox;
+    const int s = base + (oz * TILE::HY + oy) * TILE::HX + ox;
 #pragma unroll
     for (int e = 0; e < 3; ++e) d[e] = (T.c[e][s] - Ci.c[e]) * Ci.ih;
     if (MOM) {
@@ -570,6 +574,22 @@ __device__ __forceinline__ void each_sub_fit(const NB& nb, const HexCell& Ci, co
   }
 }
 
+// Row of the big stencil's least squares: the means over a neighbour (scaled
+// offset d, scaled second moments mo) of the nine zero-mean basis functions
+// of cell i.
+__device__ __forceinline__ void big_row(const double (&d)[3], const double (&mo)[6], const HexCell& Ci,
+                                        double (&r)[9]) {
+  r[0] = d[0];
+  r[1] = d[1];
+  r[2] = d[2];
+  r[3] = mo[0] + d[0] * d[0] - Ci.m[0];
+  r[4] = mo[1] + d[1] * d[1] - Ci.m[1];
+  r[5] = mo[2] + d[2] * d[2] - Ci.m[2];
+  r[6] = mo[3] + d[0] * d[1] - Ci.m[3];
+  r[7] = mo[4] + d[1] * d[2] - Ci.m[4];
+  r[8] = mo[5] + d[0] * d[2] - Ci.m[5];
+}
+
 // Quadratic least squares of the big stencil for all five variables: the
 // row of neighbour o is the mean over o of (X, X_x^2 - m_xx, ...,
 // X_x X_z - m_xz) in the scaled basis of cell i.  The 18 rows of S come
@@ -587,15 +607,7 @@ __device__ __forceinline__ void big_fit(const NB& nb, const NF& far, const HexCe
     for (int e = 0; e < 9; ++e) a[v][e] = 0.0;
   auto add_row = [&](const double (&d)[3], const double (&mo)[6], const double (&dq)[5]) {
     double r[9];
-    r[0] = d[0];
-    r[1] = d[1];
-    r[2] = d[2];
-    r[3] = mo[0] + d[0] * d[0] - Ci.m[0];
-    r[4] = mo[1] + d[1] * d[1] - Ci.m[1];
-    r[5] = mo[2] + d[2] * d[2] - Ci.m[2];
-    r[6] = mo[3] + d[0] * d[1] - Ci.m[3];
-    r[7] = mo[4] + d[1] * d[2] - Ci.m[4];
-    r[8] = mo[5] + d[0] * d[2] - Ci.m[5];
+    big_row(d, mo, Ci, r);
 #pragma unroll
     for (int p = 0; p < 9; ++p)
 #pragma unroll
@@ -659,17 +671,17 @@ __device__ __forceinline__ double pbasis(int n, const double (&X)[3], const doub
 }
 
 // Stages the reconstruction tile with origin (o0, o1, o2) and one layer
-// around it in LDS: per tile cell the centroid of its periodic image (shift
-// included), the central second moments and the five variables.
+// around it in LDS, by a workgroup of LANES lanes.
+template <int LANES, typename TILE>
 __device__ __forceinline__ void stage_hex_tile(const HexGrid& H, const double* __restrict__ geo,
                                                const double* __restrict__ q, size_t N, int o0, int o1, int o2,
-                                               HexTile& T) {
+                                               TILE& T) {
   // A tile with its layer reaches at most one period past either end when
   // every extent is at least the tile's (uniform test); a very small grid
   // may be passed several times and takes the general wrap.
-  const bool one_period = H.n[0] >= kTX && H.n[1] >= kTY && H.n[2] >= kTZ;
-  for (int t = threadIdx.x; t < kHalo; t += kBlock) {
-    const int g[3] = {o0 + t % kHX - 1, o1 + (t / kHX) % kHY - 1, o2 + t / (kHX * kHY) - 1};
+  const bool one_period = H.n[0] >= TILE::TX && H.n[1] >= TILE::TY && H.n[2] >= TILE::TZ;
+  for (int t = threadIdx.x; t < TILE::HALO; t += LANES) {
+    const int g[3] = {o0 + t % TILE::HX - 1, o1 + (t / TILE::HX) % TILE::HY - 1, o2 + t / (TILE::HX * TILE::HY) - 1};
     int c[3];
     double sh[3];
 #pragma unroll
@@ -739,13 +751,13 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))
   if (b >= ntiles) return;
   const int tx = (int)(b % ntx), ty = (int)((b / ntx) % nty), tz = (int)(b / (ntx * nty));
   const int o0 = tx * kTX, o1 = ty * kTY, o2 = tz * kTZ;
-  stage_hex_tile(H, geo, q, N, o0, o1, o2, T);
+  stage_hex_tile<kBlock>(H, geo, q, N, o0, o1, o2, T);
   __syncthreads();
   const int lx = threadIdx.x % kTX, ly = (threadIdx.x / kTX) % kTY, lz = threadIdx.x / (kTX * kTY);
   const int i = o0 + lx, j = o1 + ly, k = o2 + lz;
   if (i >= H.n[0] || j >= H.n[1] || k >= H.n[2]) return;
   const size_t idx = ((size_t)k * H.n[1] + j) * H.n[0] + i;
-  const NbrTile nb{T, ((lz + 1) * kHY + (ly + 1)) * kHX + (lx + 1)};
+  const NbrTile<HexTile> nb{T, ((lz + 1) * HexTile::HY + (ly + 1)) * HexTile::HX + (lx + 1)};
   const NbrGlobal far{H, geo, q, N, i, j, k};
   HexCell Ci;
   load_cell(geo, N, idx, Ci);

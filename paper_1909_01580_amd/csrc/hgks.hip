@@ -433,8 +433,10 @@ hgks_status hex_stage(hgks_ctx c, const double* qin, double dt, double alpha) {
     // six per-face reconstructions in characteristic variables; the
     // component-wise one above supplies the fallback mask
     prof_mark(c, HGKS_PHASE_RECON, true);
-    hipLaunchKernelGGL((k_char_recon_hex<TC>), dim3(pad8(ntiles)), dim3(kBlock), 0, c->stream, H, c->geo(), qin,
-                       (TC*)c->coef() + c->G.fs_stride, c->G.fs_stride, P, c->cfg.gamma, N, ntx, nty, ntiles);
+    const unsigned qtx = (unsigned)((c->D.n[0] + kQX - 1) / kQX), qty = (unsigned)((c->D.n[1] + kQY - 1) / kQY);
+    const unsigned qtiles = qtx * qty * (unsigned)((c->D.n[2] + kQZ - 1) / kQZ);
+    hipLaunchKernelGGL((k_char_recon_hex<TC>), dim3(pad8(qtiles)), dim3(kQLanes), 0, c->stream, H, c->geo(), qin,
+                       (TC*)c->coef() + c->G.fs_stride, c->G.fs_stride, P, c->cfg.gamma, N, qtx, qty, qtiles);
     prof_mark(c, HGKS_PHASE_RECON, false);
     if (hgks_status s = launched(c, "characteristic recon")) return s;
   }
