@@ -372,7 +372,7 @@ struct HexTileOf {
 };
 
 // Tile of the component-wise reconstruction.
-constexpr int kTX = 8, kTY = 8, kTZ = 4;
+constexpr int kTX = 8, kTY = 4, kTZ = 4, kTLanes = kTX * kTY * kTZ;
 using HexTile = HexTileOf<kTX, kTY, kTZ>;
 
 template <typename TILE>
@@ -741,17 +741,16 @@ __device__ __forceinline__ double hex_beta0(const double (&c)[9], const HexCell&
 // WIDE: the stencils of Remark 1 (the six far cells of the big stencil are
 // read from global memory, the tile holds one layer).
 template <typename TS, bool WIDE = false>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) k_recon_hex(HexGrid H, const double* __restrict__ geo,
+__global__ void __launch_bounds__(kTLanes) __attribute__((amdgpu_waves_per_eu(2))) k_recon_hex(HexGrid H, const double* __restrict__ geo,
                                                       const double* __restrict__ q, TS* __restrict__ coef,
                                                       uint32_t* __restrict__ mask, WenoParams<double> P, double gm1,
                                                       size_t N, unsigned ntx, unsigned nty, unsigned ntiles) {
-  static_assert(kTX * kTY * kTZ == kBlock, "one lane per tile cell");
   __shared__ HexTile T;
   const unsigned b = xcd_block(blockIdx.x, gridDim.x);
   if (b >= ntiles) return;
   const int tx = (int)(b % ntx), ty = (int)((b / ntx) % nty), tz = (int)(b / (ntx * nty));
   const int o0 = tx * kTX, o1 = ty * kTY, o2 = tz * kTZ;
-  stage_hex_tile<kBlock>(H, geo, q, N, o0, o1, o2, T);
+  stage_hex_tile<kTLanes>(H, geo, q, N, o0, o1, o2, T);
   __syncthreads();
   const int lx = threadIdx.x % kTX, ly = (threadIdx.x / kTX) % kTY, lz = threadIdx.x / (kTX * kTY);
   const int i = o0 + lx, j = o1 + ly, k = o2 + lz;

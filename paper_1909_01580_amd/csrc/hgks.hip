@@ -412,10 +412,10 @@ hgks_status hex_stage(hgks_ctx c, const double* qin, double dt, double alpha) {
   const unsigned ntx = (unsigned)((c->D.n[0] + kTX - 1) / kTX), nty = (unsigned)((c->D.n[1] + kTY - 1) / kTY);
   const unsigned ntiles = ntx * nty * (unsigned)((c->D.n[2] + kTZ - 1) / kTZ);
   if (c->cfg.stencil)
-    hipLaunchKernelGGL((k_recon_hex<TC, true>), dim3(pad8(ntiles)), dim3(kBlock), 0, c->stream, H, c->geo(), qin,
+    hipLaunchKernelGGL((k_recon_hex<TC, true>), dim3(pad8(ntiles)), dim3(kTLanes), 0, c->stream, H, c->geo(), qin,
                        (TC*)c->coef(), c->mask(), P, c->cfg.gamma - 1.0, N, ntx, nty, ntiles);
   else
-    hipLaunchKernelGGL((k_recon_hex<TC>), dim3(pad8(ntiles)), dim3(kBlock), 0, c->stream, H, c->geo(), qin,
+    hipLaunchKernelGGL((k_recon_hex<TC>), dim3(pad8(ntiles)), dim3(kTLanes), 0, c->stream, H, c->geo(), qin,
                        (TC*)c->coef(), c->mask(), P, c->cfg.gamma - 1.0, N, ntx, nty, ntiles);
   prof_mark(c, HGKS_PHASE_RECON, false);
   if (hgks_status s = launched(c, "recon")) return s;
