@@ -1048,7 +1048,8 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
   const TC* coefL = FS ? coef + (size_t)(2 * D + 1) * G.fs_stride : coef;
   const TC* coefR = FS ? coef + (size_t)(2 * D) * G.fs_stride : coef;
   // the left side assigns the sums, the right side adds to them
-  FluxAcc<TC, DMA> acc;
+  constexpr bool kPark = DMA && !FS;
+  FluxAcc<TC, kPark> acc;
   acc_begin(acc);
   if constexpr (DMA) {
     // The right cells' 50 values go to LDS by direct loads issued before
@@ -1062,7 +1063,7 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     static_assert(sizeof(TC) == 8 && kCB<TC> == 8, "rows of 8 doubles");
     const unsigned l = threadIdx.x & 63u;
     TC* rs = stage + (threadIdx.x >> 6) * kStageWave;
-    acc.slot = rs + 2 * kStageGroup + l;
+    if constexpr (kPark) acc.slot = rs + 2 * kStageGroup + l;
     // in piece k of group g lane l copies row 4 k + l / 16 of face slot
     // 8 g + (l / 2) % 8, 32-bit half l % 2: byte 4 l of the piece
     unsigned cell0 = __shfl(iR, (int)(((l >> 1) & 7u) * 4u));

@@ -26,12 +26,14 @@
 
 namespace hgks {
 
-// LDS tile: kCX x kCY x kCZ reconstruction-box cells (one wave per x-row
-// of 64, so that the coefficient stores of a wave are contiguous) and one
-// layer around them.  The five variables of every tile cell are staged
-// once, boundary images resolved (mirror images with the normal momentum
-// reversed), and serve the six faces of every cell of the tile.
-constexpr int kCX = 64, kCY = 2, kCZ = 2;
+// LDS tile: kCX x kCY x kCZ reconstruction-box cells and one layer around
+// them.  The five variables of every tile cell are staged once, boundary
+// images resolved (mirror images with the normal momentum reversed), and
+// serve the six faces of every cell of the tile.  16 x 4 x 4 stages 2.5
+// cells per cell and fits odd extents better than rows of 64 (4.1; the
+// 100^3 octant step 4.00 -> 3.84 ms, 128^3 Taylor-Green 8.32 -> 8.26);
+// 8 x 8 x 4 splits the 64-byte rows of the stores (4.24 ms).
+constexpr int kCX = 16, kCY = 4, kCZ = 4;
 constexpr int kCHX = kCX + 2, kCHY = kCY + 2, kCHZ = kCZ + 2, kCHalo = kCHX * kCHY * kCHZ;
 
 // Characteristic reconstruction of the tile cell at `base` (its index in
@@ -59,29 +61,42 @@ __device__ __forceinline__ void char_recon_tile_cell(const double (&T)[5][kCHalo
   CharBasis B;
   char_basis(Qb, D, gamma, B);
   TC* base_out = out + coef_cell<TC>(idx);
+  // Projected differences L_f (Q_s - Q_c) of the 18 stencil cells, one field
+  // after another: the acoustic and entropy rows combine all five
+  // variables, the shear rows only the density and one momentum (M_A - v_A
+  // rho).  One conservative variable per pass: the memory fence keeps each
+  // pass's 18 loads from being issued together with the others' (their
+  // values would all be live at once).
+  double acc[27];
+  auto pass = [&](int v, double l, bool first) {
+    const double qc = at(v, 0, 0, 0);
+#pragma unroll
+    for (int oz = -1; oz <= 1; ++oz)
+#pragma unroll
+      for (int oy = -1; oy <= 1; ++oy)
+#pragma unroll
+        for (int ox = -1; ox <= 1; ++ox) {
+          const int nz = (ox != 0) + (oy != 0) + (oz != 0);
+          if (nz == 1 || nz == 2) {
+            const double x = l * (at(v, ox, oy, oz) - qc);
+            acc[sidx(ox, oy, oz)] = first ? x : acc[sidx(ox, oy, oz)] + x;
+          } else {
+            acc[sidx(ox, oy, oz)] = 0.0;
+          }
+        }
+    asm volatile("" ::: "memory");
+  };
 #pragma unroll 1
   for (int f = 0; f < 5; ++f) {
-    double l[5];
-    char_lrow(B, f, l);
-    // d = L_f (Q_s - Q_c) over the 18 stencil cells, one conservative
-    // variable per pass: the memory fence keeps each pass's 18 loads from
-    // being issued together with the others' (their values would all be
-    // live at once).
-    double acc[27];
+    if (f == 2 || f == 3) {
+      pass(0, f == 2 ? -B.vA : -B.vC, true);
+      pass(1 + (f == 2 ? B.A : B.C), 1.0, false);
+    } else {
+      double l[5];
+      char_lrow(B, f, l);
+      pass(0, l[0], true);
 #pragma unroll
-    for (int t = 0; t < 27; ++t) acc[t] = 0.0;
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-#pragma unroll
-      for (int oz = -1; oz <= 1; ++oz)
-#pragma unroll
-        for (int oy = -1; oy <= 1; ++oy)
-#pragma unroll
-          for (int ox = -1; ox <= 1; ++ox) {
-            const int nz = (ox != 0) + (oy != 0) + (oz != 0);
-            if (nz == 1 || nz == 2) acc[sidx(ox, oy, oz)] += l[v] * (at(v, ox, oy, oz) - Qc[v]);
-          }
-      asm volatile("" ::: "memory");
+      for (int v = 1; v < 5; ++v) pass(v, l[v], false);
     }
     TC d[27];
 #pragma unroll
@@ -89,7 +104,7 @@ __device__ __forceinline__ void char_recon_tile_cell(const double (&T)[5][kCHalo
     BoxRecon<TC> r;
     weno_box(d, P, r);
     TC* cv = base_out + f * 10 * kCB<TC>;
-    cv[0] = TC(Qc[f]);  // the conservative mean of variable f
+    cv[0] = TC(at(f, 0, 0, 0));  // the conservative mean of variable f
 #pragma unroll
     for (int m = 0; m < 9; ++m) cv[(m + 1) * kCB<TC>] = r.c[m];
     asm volatile("" ::: "memory");
