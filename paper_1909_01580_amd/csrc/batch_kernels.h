@@ -210,7 +210,7 @@ template <typename TC, bool LOOP>
 __global__ void __launch_bounds__(kBlock) k_batch_dt_part(const BatchGrid<TC>* __restrict__ B, int ng,
                                                           unsigned ntiles, const double* __restrict__ q, double gamma,
                                                           double* __restrict__ part) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[kBlock / 64];
   for_tiles<LOOP>(ntiles, [&](unsigned t) {
     const int g = batch_grid_of<TC, false>(B, ng, t);
     const BatchGrid<TC>& b = B[g];
@@ -240,7 +240,7 @@ template <typename TC>
 __global__ void __launch_bounds__(kBlock) k_batch_dt_final(const BatchGrid<TC>* __restrict__ B,
                                                            const double* __restrict__ part, double cfl,
                                                            double* __restrict__ dt, uint32_t* __restrict__ status) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[kBlock / 64];
   const int g = blockIdx.x;
   double v = 1e300;
   for (unsigned t = threadIdx.x; t < B[g].nt_cell; t += kBlock) v = fmin(v, part[B[g].t_cell + t]);
@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_dt_final(const BatchGrid<TC>* 
 template <typename TC>
 __global__ void __launch_bounds__(kBlock) k_batch_totals(const BatchGrid<TC>* __restrict__ B,
                                                          const double* __restrict__ q, double* __restrict__ out) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[kBlock / 64];
   const int g = blockIdx.x;
   const BatchGrid<TC>& b = B[g];
   for (int v = 0; v < 5; ++v) {

@@ -500,18 +500,20 @@ __device__ __forceinline__ bool recon_box_cell(const double* __restrict__ q, TC*
   BoxNbr<WIDE> B;
   box_nbr(G, idx, B);
   TC qc[5], bnd[5];
+  size_t later = 0;  // added to the array's base
   auto var = [&](auto vc) {
     constexpr int V = decltype(vc)::value;
     double c;
     BoxRecon<TC> r;
-    recon_box_var<V, TC, WIDE>(q, G, B, P, c, r);
+    recon_box_var<V, TC, WIDE>(q + later, G, B, P, c, r);
     if constexpr (COEF) store_recon(coef, idx, V, c, r);
     qc[V] = TC(c);
     bnd[V] = r.bound;
     // The next variable's stencil loads wait for this variable's results
-    // (an empty asm ties their indices to them), so the compiler does not
-    // hoist all five stencils ahead and hold them in registers at once.
-    asm volatile("" : "+v"(B.iz[0]), "+v"(B.iz[1]), "+v"(B.iz[2]) : "v"(r.c[0]), "v"(r.bound));
+    // (an empty asm ties the array's base to them), so the compiler does not
+    // hoist all five stencils ahead and hold them in registers at once; the
+    // 19 lane offsets serve all five.
+    asm volatile("" : "+s"(later) : "v"(r.c[0]), "v"(r.bound));
   };
   var(std::integral_constant<int, 0>());
   var(std::integral_constant<int, 1>());
@@ -1278,16 +1280,17 @@ __global__ void __launch_bounds__(kBlock) k_update_box(double* __restrict__ q, d
 }
 
 // ---------------------------------------------------------------- reductions
+// v combined over the workgroup's lanes (kBlock) in a fixed order: lane
+// shuffles within a wave, then the waves' values through sh.  A second
+// reduction with the same sh needs a barrier between.
 template <typename T, typename Op>
 __device__ __forceinline__ T block_reduce(T v, T* sh, Op op) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
 #pragma unroll
-  for (int s = kBlock / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] = op(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
-  }
-  return sh[0];
+  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o));
+  if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  static_assert(kBlock == 256, "four waves");
+  return op(op(sh[0], sh[1]), op(sh[2], sh[3]));
 }
 
 struct MinOp {
@@ -1298,29 +1301,40 @@ struct SumOp {
   __device__ T operator()(T a, T b) const { return a + b; }
 };
 
+// Reductions over the cells run on at most kRedBlocks workgroups, each
+// walking its cells with a fixed stride, so that the one workgroup that
+// combines the partial results has few of them (65,536 partials of the 256^3
+// grid took it 90 us, 8,192 of 128^3 11 us; 1,024 take 3 us).
+constexpr unsigned kRedBlocks = 1024;
+
+template <typename F>
+__device__ __forceinline__ void for_cells(size_t N, F&& body) {
+  for (size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x; idx < N; idx += (size_t)gridDim.x * kBlock) body(idx);
+}
+
 // Time-step bound h / (|U| + c) per cell, minimum per block.
 __global__ void __launch_bounds__(kBlock) k_dt_box(const double* __restrict__ q, BoxGrid G, double gamma,
                                                    double* __restrict__ part, size_t N) {
-  __shared__ double sh[kBlock];
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  double v = 1e300;
-  if (idx < N) {
+  __shared__ double sh[kBlock / 64];
+  double h = 1.0 / G.inv_dx[0];
+  h = fmin(h, 1.0 / G.inv_dx[1]);
+  h = fmin(h, 1.0 / G.inv_dx[2]);
+  double least = 1e300;
+  for_cells(N, [&](size_t idx) {
     const double rho = q[idx];
     const double u = q[N + idx] / rho, w1 = q[2 * N + idx] / rho, w2 = q[3 * N + idx] / rho;
     const double p = (gamma - 1.0) * (q[4 * N + idx] - 0.5 * rho * (u * u + w1 * w1 + w2 * w2));
     const double c = sqrt(gamma * p / rho);
-    double h = 1.0 / G.inv_dx[0];
-    h = fmin(h, 1.0 / G.inv_dx[1]);
-    h = fmin(h, 1.0 / G.inv_dx[2]);
-    v = h / (sqrt(u * u + w1 * w1 + w2 * w2) + c);
-    if (!(v > 0.0)) v = -1.0;  // non-physical state: reported as a negative bound
-  }
-  const double r = block_reduce(v, sh, MinOp());
+    const double v = h / (sqrt(u * u + w1 * w1 + w2 * w2) + c);
+    // a non-physical state is reported as a negative bound
+    least = fmin(least, v > 0.0 ? v : -1.0);
+  });
+  const double r = block_reduce(least, sh, MinOp());
   if (threadIdx.x == 0) part[blockIdx.x] = r;
 }
 
 __global__ void __launch_bounds__(kBlock) k_min_final(const double* __restrict__ part, int n, double* __restrict__ out) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[kBlock / 64];
   double v = 1e300;
   for (int i = threadIdx.x; i < n; i += kBlock) v = fmin(v, part[i]);
   const double r = block_reduce(v, sh, MinOp());
@@ -1328,50 +1342,54 @@ __global__ void __launch_bounds__(kBlock) k_min_final(const double* __restrict__
 }
 
 // sum |Omega| Q_v: fixed-order block sums, then a fixed-order final sum.
-__global__ void __launch_bounds__(kBlock) k_totals_box(const double* __restrict__ q, double vol,
-                                                       double* __restrict__ part, size_t N, int nblk) {
-  __shared__ double sh[kBlock];
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
+// geo = null: every cell has volume vol; else the hexahedral geometry
+// record, whose first row is the cell volume.
+__global__ void __launch_bounds__(kBlock) k_totals(const double* __restrict__ q, const double* __restrict__ geo,
+                                                   double vol, double* __restrict__ part, size_t N, int nblk) {
+  __shared__ double sh[5][kBlock / 64];
+  double x[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for_cells(N, [&](size_t idx) {
+    const double V = geo ? geo[idx] : vol;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) x[v] += q[(size_t)v * N + idx] * V;
+  });
+#pragma unroll
   for (int v = 0; v < 5; ++v) {
-    const double x = idx < N ? q[(size_t)v * N + idx] * vol : 0.0;
-    const double r = block_reduce(x, sh, SumOp());
+    const double r = block_reduce(x[v], sh[v], SumOp());
     if (threadIdx.x == 0) part[(size_t)v * nblk + blockIdx.x] = r;
-    __syncthreads();
   }
 }
 
 // Kinetic energy of the cell averages, sum |Omega_i| |M_i|^2 / (2 rho_i)
 // (the integrand of the volume-averaged kinetic energy of Sec. 4, Taylor-
 // Green vortex, taken on the cell averages), and the volume sum |Omega_i|,
-// per block in a fixed order.  geo = null: every cell has volume vol; else
-// the hexahedral geometry record, whose first row is the cell volume.
+// per block in a fixed order; geo as above.
 __global__ void __launch_bounds__(kBlock) k_kinetic(const double* __restrict__ q, const double* __restrict__ geo,
                                                     double vol, double* __restrict__ part, size_t N, int nblk) {
-  __shared__ double sh[kBlock];
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  __shared__ double sh[2][kBlock / 64];
   double e = 0.0, v = 0.0;
-  if (idx < N) {
+  for_cells(N, [&](size_t idx) {
     const double V = geo ? geo[idx] : vol;
     const double m2 = q[N + idx] * q[N + idx] + q[2 * N + idx] * q[2 * N + idx] + q[3 * N + idx] * q[3 * N + idx];
-    e = V * 0.5 * m2 / q[idx];
-    v = V;
+    e += V * 0.5 * m2 / q[idx];
+    v += V;
+  });
+  const double r1 = block_reduce(e, sh[0], SumOp()), r2 = block_reduce(v, sh[1], SumOp());
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = r1;
+    part[(size_t)nblk + blockIdx.x] = r2;
   }
-  const double r1 = block_reduce(e, sh, SumOp());
-  if (threadIdx.x == 0) part[blockIdx.x] = r1;
-  __syncthreads();
-  const double r2 = block_reduce(v, sh, SumOp());
-  if (threadIdx.x == 0) part[(size_t)nblk + blockIdx.x] = r2;
 }
 
+// out[v] = sum of the n partials of row v, for nvec <= 5 rows.
 __global__ void __launch_bounds__(kBlock) k_sum_final(const double* __restrict__ part, int n, int nvec,
                                                       double* __restrict__ out) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[5][kBlock / 64];
   for (int v = 0; v < nvec; ++v) {
     double x = 0.0;
     for (int i = threadIdx.x; i < n; i += kBlock) x += part[(size_t)v * n + i];
-    const double r = block_reduce(x, sh, SumOp());
+    const double r = block_reduce(x, sh[v], SumOp());
     if (threadIdx.x == 0) out[v] = r;
-    __syncthreads();
   }
 }
 
@@ -1379,25 +1397,24 @@ __global__ void __launch_bounds__(kBlock) k_sum_final(const double* __restrict__
 __global__ void __launch_bounds__(kBlock) k_check_box(const double* __restrict__ q, const uint32_t* __restrict__ mask,
                                                       BoxGrid G, double gamma, double* __restrict__ part,
                                                       size_t N, int nblk) {
-  __shared__ double sh[kBlock];
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  __shared__ double sh[2][kBlock / 64];
   double bad = 0.0, fb = 0.0;
-  if (idx < N) {
+  for_cells(N, [&](size_t idx) {
     const double rho = q[idx];
     const double e = q[4 * N + idx];
     const double m2 = q[N + idx] * q[N + idx] + q[2 * N + idx] * q[2 * N + idx] + q[3 * N + idx] * q[3 * N + idx];
     const double p = (gamma - 1.0) * (e - 0.5 * m2 / rho);
-    bad = (rho > 0.0 && p > 0.0) ? 0.0 : 1.0;
-    const int c0 = (int)(idx % G.n[0]), c1 = (int)((idx / G.n[0]) % G.n[1]);
-    const int c2 = (int)(idx / ((size_t)G.n[0] * G.n[1]));
+    bad += (rho > 0.0 && p > 0.0) ? 0.0 : 1.0;
+    int c0, c1, c2;
+    split_index((uint32_t)idx, G.n[0], G.n[1], G.inv_n[0], G.inv_n[1], c0, c1, c2);
     const size_t r = ((size_t)(c2 + G.g[2]) * G.nr[1] + (c1 + G.g[1])) * G.nr[0] + (c0 + G.g[0]);
-    fb = (double)__popc(mask[r] & 0x00FFFFFFu);
+    fb += (double)__popc(mask[r] & 0x00FFFFFFu);
+  });
+  const double r1 = block_reduce(bad, sh[0], SumOp()), r2 = block_reduce(fb, sh[1], SumOp());
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = r1;
+    part[(size_t)nblk + blockIdx.x] = r2;
   }
-  double r1 = block_reduce(bad, sh, SumOp());
-  if (threadIdx.x == 0) part[blockIdx.x] = r1;
-  __syncthreads();
-  double r2 = block_reduce(fb, sh, SumOp());
-  if (threadIdx.x == 0) part[(size_t)nblk + blockIdx.x] = r2;
 }
 
 // ---------------------------------------------------------------- debug

@@ -1467,51 +1467,43 @@ __global__ void __launch_bounds__(kBlock) k_update_hex(HexGrid H, double* __rest
 // ---------------------------------------------------------------- reductions
 __global__ void __launch_bounds__(kBlock) k_dt_hex(HexGrid H, const double* __restrict__ q, double gamma,
                                                    double* __restrict__ part, size_t N) {
-  __shared__ double sh[kBlock];
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  double val = 1e300;
-  if (idx < N) {
+  __shared__ double sh[kBlock / 64];
+  double least = 1e300;
+  for_cells(N, [&](size_t idx) {
     int i, j, k;
-  split_index((uint32_t)idx, H.n[0], H.n[1], H.box.inv_n[0], H.box.inv_n[1], i, j, k);
+    split_index((uint32_t)idx, H.n[0], H.n[1], H.box.inv_n[0], H.box.inv_n[1], i, j, k);
+    // centres of the six faces: the cell's vertices are its lattice point
+    // and the +1 neighbours
     double cx[8][3];
-    for (int m = 0; m < 8; ++m) {
-      double u[3];
-      hex_vertex(H, i + ((m >> 2) & 1), j + ((m >> 1) & 1), k + (m & 1), cx[m], u);
-    }
+    const CellVerts cv = cell_verts(H, i, j, k);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) cell_vertex(H, cv, m, cx[m]);
     double hmin = 1e300;
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
       const int bit = 4 >> d;
-      double lo[3] = {0, 0, 0}, up[3] = {0, 0, 0};
-      for (int m = 0; m < 8; ++m)
-        for (int e = 0; e < 3; ++e) {
-          if (m & bit) up[e] += 0.25 * cx[m][e];
-          else lo[e] += 0.25 * cx[m][e];
+      double gap[3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        double lo = 0.0, up = 0.0;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          if (m & bit) up += 0.25 * cx[m][e];
+          else lo += 0.25 * cx[m][e];
         }
-      const double dd = sqrt((up[0] - lo[0]) * (up[0] - lo[0]) + (up[1] - lo[1]) * (up[1] - lo[1]) +
-                             (up[2] - lo[2]) * (up[2] - lo[2]));
-      hmin = fmin(hmin, dd);
+        gap[e] = up - lo;
+      }
+      hmin = fmin(hmin, sqrt(gap[0] * gap[0] + gap[1] * gap[1] + gap[2] * gap[2]));
     }
     const double rho = q[idx];
     const double u = q[N + idx] / rho, v = q[2 * N + idx] / rho, w = q[3 * N + idx] / rho;
     const double p = (gamma - 1.0) * (q[4 * N + idx] - 0.5 * rho * (u * u + v * v + w * w));
     const double c = sqrt(gamma * p / rho);
-    val = hmin / (sqrt(u * u + v * v + w * w) + c);
-    if (!(val > 0.0)) val = -1.0;
-  }
-  const double r = block_reduce(val, sh, MinOp());
+    const double val = hmin / (sqrt(u * u + v * v + w * w) + c);
+    least = fmin(least, val > 0.0 ? val : -1.0);
+  });
+  const double r = block_reduce(least, sh, MinOp());
   if (threadIdx.x == 0) part[blockIdx.x] = r;
-}
-
-__global__ void __launch_bounds__(kBlock) k_totals_hex(const double* __restrict__ q, const double* __restrict__ geo,
-                                                       double* __restrict__ part, size_t N, int nblk) {
-  __shared__ double sh[kBlock];
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  for (int v = 0; v < 5; ++v) {
-    const double x = idx < N ? q[(size_t)v * N + idx] * geo[idx] : 0.0;
-    const double r = block_reduce(x, sh, SumOp());
-    if (threadIdx.x == 0) part[(size_t)v * nblk + blockIdx.x] = r;
-    __syncthreads();
-  }
 }
 
 // ---------------------------------------------------------------- debug
