@@ -165,7 +165,7 @@ struct hgks_ctx_s {
   char* ws;
   bool grid_set = false, state_set = false, next_set = false;
   hgks_status sticky = HGKS_OK;
-  double* host = nullptr;  // pinned: results of the reductions
+  double* host = nullptr;  // slot of pinned host memory for the results of the reductions
   double period[3];
   // Phase timing (hgks_profile_begin / hgks_profile_end).
   static constexpr int kProfCap = 512;
@@ -572,10 +572,45 @@ hgks_status set_box(hgks_ctx c, const double origin[3], const double length[3]) 
   return HGKS_OK;
 }
 
-// Where a reduction writes its result (at most 8 doubles): the context's
-// pinned host memory, which the device addresses, or without it device
-// scratch.
-double* result(hgks_ctx c) { return c->host ? c->host : c->red() + c->D.nred - 8; }
+// Pinned host memory for the results of the reductions: one page per
+// process, allocated at the first reduction and kept, in slots of 8 doubles
+// that contexts take at their first reduction and give back when destroyed
+// (creating and destroying a context makes no device call, so both stay
+// possible while a stream is being captured).  A context that finds no slot
+// left, or no page, has its results copied from device scratch.
+constexpr int kResultSlots = 64;
+std::mutex g_result_mu;
+double* g_result_page = nullptr;
+bool g_result_tried = false;
+uint64_t g_result_free = ~0ull;
+
+double* result_slot() {
+  std::lock_guard<std::mutex> lock(g_result_mu);
+  if (!g_result_tried) {
+    g_result_tried = true;
+    if (hipHostMalloc((void**)&g_result_page, kResultSlots * 8 * sizeof(double), hipHostMallocPortable) !=
+        hipSuccess) {
+      g_result_page = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  if (!g_result_page || !g_result_free) return nullptr;
+  const int k = __builtin_ctzll(g_result_free);
+  g_result_free &= g_result_free - 1;
+  return g_result_page + 8 * k;
+}
+
+void result_slot_back(double* p) {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(g_result_mu);
+  g_result_free |= 1ull << ((p - g_result_page) / 8);
+}
+
+// Where a reduction writes its result (at most 8 doubles).
+double* result(hgks_ctx c) {
+  if (!c->host) c->host = result_slot();
+  return c->host ? c->host : c->red() + c->D.nred - 8;
+}
 
 // Waits for the stream and gives the n results.  From pinned memory there is
 // no copy to wait for: the 16^3 advection step, whose time step is reduced
@@ -583,8 +618,9 @@ double* result(hgks_ctx c) { return c->host ? c->host : c->red() + c->D.nred - 8
 // the shorter reductions.
 hgks_status fetch_result(hgks_ctx c, int n, double* out) {
   if (!c->host)
-    if (hgks_status s = check_hip(c, hipMemcpyAsync(out, result(c), n * sizeof(double), hipMemcpyDeviceToHost,
-                                                    c->stream), "copy"))
+    if (hgks_status s = check_hip(c, hipMemcpyAsync(out, c->red() + c->D.nred - 8, n * sizeof(double),
+                                                    hipMemcpyDeviceToHost, c->stream),
+                                  "copy"))
       return s;
   if (hgks_status s = check_hip(c, hipStreamSynchronize(c->stream), "synchronise")) return s;
   if (c->host) std::memcpy(out, c->host, n * sizeof(double));
@@ -635,11 +671,6 @@ hgks_status hgks_create(const hgks_config* cfg, void* workspace_dev, size_t byte
     delete c;
     return fail(HGKS_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, need);
   }
-  // results then come through device scratch and a copy
-  if (hipHostMalloc((void**)&c->host, 8 * sizeof(double), hipHostMallocPortable) != hipSuccess) {
-    c->host = nullptr;
-    (void)hipGetLastError();
-  }
   *out = c;
   return HGKS_OK;
 }
@@ -648,7 +679,7 @@ hgks_status hgks_destroy(hgks_ctx ctx) {
   if (ctx) {
     for (int p = 0; p < HGKS_NPHASES; ++p)
       for (auto& e : ctx->prof_ev[p]) hipEventDestroy(e);
-    if (ctx->host) (void)hipHostFree(ctx->host);
+    result_slot_back(ctx->host);
   }
   delete ctx;
   return HGKS_OK;
