@@ -99,11 +99,12 @@ struct FluxAcc {
 };
 
 // How the first side of a face enters the sums: assigned (true) or added to
-// zeroed sums (false).  The values are the same; assigning issues about 35
-// fewer adds and 45 fewer register clears per Gauss point.  Measured on
-// gfx950 it shortens the FP64 flux launch by about 1% but lengthens the FP32
-// one by about 3% (the compiler's schedule of the mixed kernel loses more
-// than the instructions save), so the choice is per precision.
+// zeroed sums (false).  The values are the same; assigning saves an add and a
+// register clear per sum.  Measured on gfx950, with longer side terms than
+// the present ones, it shortened the FP64 flux launch by about 1% but
+// lengthened the FP32 one by about 3% (the compiler's schedule of the mixed
+// kernel lost more than the instructions saved), so the choice is per
+// precision.
 template <typename T>
 inline constexpr bool kAssignFirst = sizeof(T) == 8;
 
