@@ -256,6 +256,21 @@ def hgks_profile_end(h):
 
 
 # ------------------------------------------------------------ wrapper
+def _wait_for_caller(stream, device):
+    """Queues a wait of ``stream`` for the work on the caller's current
+    stream: a tensor that it reads may still be written there, and the memory
+    of a fresh one may still be in use there by the tensor that held it
+    before.  Returns the caller's stream, or None where no order is needed
+    (one stream) or possible (while the caller's stream is being captured
+    nothing queued on it runs, and a wait would draw ``stream`` into the
+    capture)."""
+    cur = torch.cuda.current_stream(device)
+    if cur == stream or torch.cuda.is_current_stream_capturing():
+        return None
+    stream.wait_stream(cur)
+    return cur
+
+
 def make_config(n, bc=("periodic",) * 3, gamma=1.4, mu=0.0, weno_Gamma=0.0025, weno_eps=1e-8, tau_eps=0.01,
                 tau_C=1.0, precision="fp64", moving=False, characteristic=False, mu_T0=1.0, mu_exponent=0.0,
                 prandtl=1.0, stencil="S", stream=None):
@@ -486,6 +501,11 @@ class Batch:
         self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
         off = (-self.workspace.data_ptr()) % 256
         self._ws = self.workspace[off:off + nbytes]
+        # the workspace comes from the caller's stream's allocator: work on
+        # the memory's last tensor may be queued there, and the batch may be
+        # dropped while its own stream still runs
+        if _wait_for_caller(stream, self.device) is not None:
+            self.workspace.record_stream(stream)
         self.h = hgks_batch_create(cfgs, self._ws)
         for i, g in enumerate(grids):
             hgks_batch_set_uniform_grid(self.h, i, g.get("origin", (0.0, 0.0, 0.0)), g["length"])
@@ -509,15 +529,26 @@ class Batch:
 
     def get_state(self, i):
         out = torch.empty(self.shape(i), dtype=torch.float64, device=self.device)
+        _wait_for_caller(self.stream, self.device)
         hgks_batch_get_state(self.h, i, out)
         hgks_batch_sync(self.h)
         return out
 
     def max_dt(self, cfl, dt=None):
+        if dt is None:  # the batch's own array
+            hgks_batch_max_dt(self.h, cfl)
+            return
+        cur = _wait_for_caller(self.stream, self.device)
         hgks_batch_max_dt(self.h, cfl, dt)
+        if cur is not None:
+            dt.record_stream(self.stream)
+            cur.wait_stream(self.stream)
 
     def step(self, dt, n_stages=2):
+        cur = _wait_for_caller(self.stream, self.device)
         hgks_batch_step(self.h, dt, n_stages)
+        if cur is not None:
+            dt.record_stream(self.stream)
 
     def set_launch(self, phase, workgroups):
         hgks_batch_set_launch(self.h, phase, workgroups)
