@@ -271,6 +271,18 @@ def _wait_for_caller(stream, device):
     return cur
 
 
+def _shared(owner, t, written, call, *args):
+    """A call that queues work on the caller's tensor ``t`` on ``owner``'s
+    stream: after the caller's stream, the allocator told of the use, and
+    where ``t`` is ``written`` the caller's stream after it."""
+    cur = _wait_for_caller(owner.stream, owner.device)
+    call(*args)
+    if cur is not None:
+        t.record_stream(owner.stream)
+        if written:
+            cur.wait_stream(owner.stream)
+
+
 def make_config(n, bc=("periodic",) * 3, gamma=1.4, mu=0.0, weno_Gamma=0.0025, weno_eps=1e-8, tau_eps=0.01,
                 tau_C=1.0, precision="fp64", moving=False, characteristic=False, mu_T0=1.0, mu_exponent=0.0,
                 prandtl=1.0, stencil="S", stream=None):
@@ -320,6 +332,9 @@ class Context:
         self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
         off = (-self.workspace.data_ptr()) % 256
         self._ws = self.workspace[off:off + nbytes]
+        # from the caller's stream's allocator, as every tensor here
+        if _wait_for_caller(stream, self.device) is not None:
+            self.workspace.record_stream(stream)
         self.h = hgks_create(cfg, self._ws)
 
     def __del__(self):
@@ -337,18 +352,18 @@ class Context:
         hgks_set_uniform_grid(self.h, origin, length)
 
     def set_vertices(self, xyz, period):
-        hgks_set_vertices(self.h, xyz, period)
+        _shared(self, xyz, False, hgks_set_vertices, self.h, xyz, period)
 
     def set_next_vertices(self, xyz):
-        hgks_set_next_vertices(self.h, xyz)
+        _shared(self, xyz, False, hgks_set_next_vertices, self.h, xyz)
 
     def set_state(self, q):
-        hgks_set_state(self.h, q)
+        _shared(self, q, False, hgks_set_state, self.h, q)
 
     def get_state(self, out=None):
         if out is None:
             out = torch.empty(self.shape, dtype=torch.float64, device=self.device)
-        hgks_get_state(self.h, out)
+        _shared(self, out, True, hgks_get_state, self.h, out)
         return out
 
     def max_dt(self, cfl):
@@ -373,19 +388,19 @@ class Context:
         """Fallback words [nz][ny][nx] (uint32 bit patterns held in int32)."""
         nx, ny, nz = self.n
         out = torch.empty((nz, ny, nx), dtype=torch.int32, device=self.device)
-        hgks_debug_fallback_mask(self.h, dt, out)
+        _shared(self, out, True, hgks_debug_fallback_mask, self.h, dt, out)
         return out
 
     def debug_gp_states(self, dt):
         nx, ny, nz = self.n
         out = torch.empty((nz, ny, nx, 24, 5, 4), dtype=torch.float64, device=self.device)
-        hgks_debug_gp_states(self.h, dt, out)
+        _shared(self, out, True, hgks_debug_gp_states, self.h, dt, out)
         return out
 
     def debug_face_flux(self, dt):
         nx, ny, nz = self.n
         out = torch.empty((3, nz, ny, nx, 2, 5), dtype=torch.float64, device=self.device)
-        hgks_debug_face_flux(self.h, dt, out)
+        _shared(self, out, True, hgks_debug_face_flux, self.h, dt, out)
         return out
 
     def sync(self):
@@ -538,17 +553,10 @@ class Batch:
         if dt is None:  # the batch's own array
             hgks_batch_max_dt(self.h, cfl)
             return
-        cur = _wait_for_caller(self.stream, self.device)
-        hgks_batch_max_dt(self.h, cfl, dt)
-        if cur is not None:
-            dt.record_stream(self.stream)
-            cur.wait_stream(self.stream)
+        _shared(self, dt, True, hgks_batch_max_dt, self.h, cfl, dt)
 
     def step(self, dt, n_stages=2):
-        cur = _wait_for_caller(self.stream, self.device)
-        hgks_batch_step(self.h, dt, n_stages)
-        if cur is not None:
-            dt.record_stream(self.stream)
+        _shared(self, dt, False, hgks_batch_step, self.h, dt, n_stages)
 
     def set_launch(self, phase, workgroups):
         hgks_batch_set_launch(self.h, phase, workgroups)

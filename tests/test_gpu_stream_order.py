@@ -147,3 +147,32 @@ def test_step_while_the_caller_captures(hg):
         torch.cuda.synchronize()
         assert x.tolist() == [float(k)] * 8
     assert torch.equal(b.get_state(0), want)
+
+
+def test_context_on_a_stream_of_its_own(hg, busy):
+    """Set, step, read and a parity hook under another current stream, with
+    either side busy, inputs dropped at once and outputs read at once."""
+    q = state(11)
+
+    def march(ctx, hold):
+        ctx.set_uniform_grid((0.0,) * 3, L)
+        got = []
+        for _ in range(3):
+            hold(None)
+            ctx.set_state(q * 1.0)
+            torch.full_like(q, 7.0)               # takes the dropped input's memory
+            ctx.step(1e-3, 2)
+            hold(ctx.stream)
+            got += [ctx.get_state() * 1.0, ctx.debug_face_flux(1e-3) * 1.0]
+        return got
+
+    def wait(stream):
+        torch.cuda.synchronize()
+
+    def work(stream):
+        with torch.cuda.stream(stream or torch.cuda.current_stream()):
+            busy()
+
+    want = march(hg.Context(N), wait)
+    for a, b in zip(march(hg.Context(N, stream=torch.cuda.Stream()), work), want):
+        assert torch.equal(a, b)

@@ -119,3 +119,36 @@ def test_nothing_is_ordered_while_the_caller_is_captured(world, monkeypatch):
     b.max_dt(0.35, Tensor("dt", log))
     b.get_state(0)
     assert not [e for e in log if e[0] == "wait"]
+
+
+def context(own):
+    c = object.__new__(hgks.Context)
+    c.device, c.stream, c.h, c.n = torch.device("cpu"), own, None, (4, 4, 4)
+    return c
+
+
+@pytest.mark.parametrize("method,args,written", [
+    ("set_state", 1, False), ("set_vertices", 2, False), ("set_next_vertices", 1, False),
+    ("get_state", 1, True), ("get_state", 0, True), ("debug_fallback_mask", 0, True),
+    ("debug_gp_states", 0, True), ("debug_face_flux", 0, True)])
+def test_context_on_another_stream(world, method, args, written):
+    """A context given a stream of its own, called under the caller's."""
+    log, own, caller = world
+    t = Tensor("t", log)
+    call = (t, (1.0,) * 3)[:args] if method.startswith(("set", "get")) else (1e-3,)
+    getattr(context(own), method)(*call)
+    launch = log.index(("call", "hgks_" + method))
+    assert CALLER_FIRST in log[:launch]
+    assert ("record", "t" if args else "new", "own") in log[launch:]
+    assert (("wait", "caller", "own") in log[launch:]) == written
+    # the usual case, one stream: the library call alone
+    del log[:]
+    getattr(context(caller), method)(*call)
+    assert log == [("call", "hgks_" + method)]
+
+
+def test_context_workspace_belongs_to_its_stream(world):
+    log, own, _ = world
+    hgks.Context((4, 4, 4), device="cpu", stream=own)
+    assert CALLER_FIRST in log[:log.index(("call", "hgks_create"))]
+    assert ("record", "new", "own") in log
