@@ -295,19 +295,13 @@ __global__ void __launch_bounds__(kQLanes) __attribute__((amdgpu_waves_per_eu(3)
 #pragma unroll
         for (int v = 0; v < 5; ++v) bu[v][e] = f[v];
       }
-      double bm[5], rm[5];
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        bm[f] = bu[f][0] * bu[f][0] + bu[f][1] * bu[f][1] + bu[f][2] * bu[f][2];
-        tsum[f] += fabs(beta0[f] - bm[f]);
-      }
-      rcp_pair(bm[0] + P.eps, bm[4] + P.eps, rm[0], rm[4]);
-      rcp_pair(bm[2] + P.eps, bm[3] + P.eps, rm[2], rm[3]);
-      rm[1] = d_rcp(bm[1] + P.eps);
-#pragma unroll
-      for (int f = 0; f < 5; ++f) {
-        rsum[f] += rm[f];
-        const double dr = rm[f] - r0[f];
+        const double bm = bu[f][0] * bu[f][0] + bu[f][1] * bu[f][1] + bu[f][2] * bu[f][2];
+        tsum[f] += fabs(beta0[f] - bm);
+        const double rm = d_rcp(bm + P.eps);
+        rsum[f] += rm;
+        const double dr = rm - r0[f];
 #pragma unroll
         for (int e = 0; e < 3; ++e) db[f][e] += dr * bu[f][e];
       }

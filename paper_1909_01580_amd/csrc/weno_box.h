@@ -59,22 +59,6 @@ HGKS_FN T lin_bound(T bx, T by, T bz) {
   return T(0.5) * (d_abs(bx) + d_abs(by) + d_abs(bz));
 }
 
-// 1/x and 1/y of positive numbers.  In double one reciprocal of the product
-// serves both (11 issue slots instead of 16: the FP64 estimate takes four);
-// the product of two indicators stays far from the ends of its range.  In
-// float it might not, and the estimate costs less: two reciprocals.
-template <typename T>
-HGKS_FN void rcp_pair(T x, T y, T& ix, T& iy) {
-  if constexpr (sizeof(T) == 8) {
-    const T r = d_rcp(x * y);
-    ix = r * y;
-    iy = r * x;
-  } else {
-    ix = d_rcp(x);
-    iy = d_rcp(y);
-  }
-}
-
 // Least-squares quadratic of the big stencil (closed form above).
 template <typename T>
 HGKS_FN void big_quadratic(const T (&d)[27], T (&a)[9]) {
@@ -188,11 +172,12 @@ HGKS_FN void weno_box(const T (&d)[27], const WenoParams<T>& P, BoxRecon<T>& out
       const T b0 = q[p] + ecp, b1 = q[p] + ecm;
       tsum += d_abs(beta0 - b0);
       tsum += d_abs(beta0 - b1);
-      T r[2];
-      rcp_pair(b0 + P.eps, b1 + P.eps, r[0], r[1]);
-      rp += r[0];
-      rm += r[1];
-      const T ds = (r[0] + r[1]) - r0_2;
+      // One reciprocal each: the product of two indicators, whose reciprocal
+      // would serve both, leaves the format for a small epsilon or large data.
+      const T rp1 = d_rcp(b0 + P.eps), rm1 = d_rcp(b1 + P.eps);
+      rp += rp1;
+      rm += rm1;
+      const T ds = (rp1 + rm1) - r0_2;
       db3[ea] += ds * (sa * ab[p]);
       db3[eb] += ds * (sb * bb3[p]);
     }
