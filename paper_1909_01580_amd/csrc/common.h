@@ -85,57 +85,93 @@ HGKS_FN T erf_small(T x, const double (&c)[N]) {
   return s * x;
 }
 
-// (1 + 2 y) exp(y^2) erfc(y) for y >= 1 as a polynomial in t = (y - 5/2) /
-// (y + 5/2), which maps y >= 1 to [-3/7, 1] (the form of Shepherd and
-// Laframboise, Math. Comp. 36 (1981) 249; the coefficients here interpolate
-// it at the Chebyshev nodes of that interval, computed in 60 digits from
-// the series and the continued fraction of erfc).  Relative error below
-// 8e-17 (double) and 1.2e-8 (float).
-constexpr double kErfcx20[21] = {
-    1.2648381843668615, -0.12235676308240334, -0.09902453957361883,
-    0.15762991902306947, -0.1029670560369499, 0.03276089327449818,
-    0.0009318927560479804, -0.004382078407562973, 0.0004918669534855608,
-    0.0006321238749692234, -8.849021316160707e-05, -0.00011350557508225432,
-    6.314854131183766e-06, 2.2557189087445965e-05, 2.58439735084272e-06,
-    -3.736015440011357e-06, -2.0969626664127912e-06, 1.9248433454712853e-07,
-    1.6811287081232611e-06, -9.341138827040256e-07, 1.5677373653870477e-07};
-constexpr double kErfcx9[10] = {
-    1.264838192458751, -0.12235658115265136, -0.09902554193976162,
-    0.15762353273444266, -0.10294296676703253, 0.032807473163065384,
-    0.00072638705545182, -0.004371426325112118, 0.0010439879858344689,
-    3.6121971193970767e-05};
+// P(t) = (1 + 2 y) exp(y^2) erfc(y) for y >= 1 as a polynomial in t = (y -
+// 5/2) / (y + 5/2) (the form of Shepherd and Laframboise, Math. Comp. 36
+// (1981) 249; the coefficients here interpolate it at the Chebyshev nodes of
+// the interval of t, computed in 60 digits).  Double: 1 <= y <= 30, relative
+// error 4e-19 before the coefficients are rounded, the first one in two
+// parts; float: 1 <= y <= 10.5, 5e-11.
+constexpr double kErfcx21[22] = {
+    1.2648381843668615, -0.1223567630824043, -0.09902453957360235,
+    0.15762991902321885, -0.10296705603851898, 0.032760893268653696,
+    0.000931892815307037, -0.004382078339872744, 0.0004918658536842841,
+    0.0006321243168957018, -8.847971929518672e-05, -0.00011352181855272056,
+    6.26936202312381e-06, 2.2693527327655664e-05, 2.5971676254965236e-06,
+    -4.181932452772929e-06, -1.58008076814213e-06, 4.254768999387085e-07,
+    6.243366585283449e-07, 1.0943714025627054e-07, -3.172387991637216e-07,
+    8.596810916622534e-08};
+constexpr double kErfcx21Low = 2.187269270200059e-17;
+constexpr double kErfcx10[11] = {
+    1.2648381844224124, -0.12235676258686475, -0.09902455259899415,
+    0.15762988884746656, -0.1029665512994253, 0.032761221394023654,
+    0.0009248454795583878, -0.004380325802225843, 0.0005328702366322006,
+    0.0005971990384327377, -0.00017215213115138133};
 
 template <typename T> HGKS_FN T d_rcp(T x);
+template <> HGKS_FN double d_rcp<double>(double x);
 
-// erfc(y) = e P(t) / (1 + 2 y) for y >= 1, e = exp(-y^2).  Beyond y = 30 e
-// is 0 in both precisions.
-template <int N, typename T>
-HGKS_FN T erfc_tail(T y, T e, const double (&c)[N]) {
-  y = y < T(30) ? y : T(30);
-  const T a = y + T(2.5), b = T(2) * y + T(1);
-  const T r = d_rcp(a * b);
-  const T t = (y - T(2.5)) * (b * r);
-  T p = T(c[N - 1]);
+// (P(t) - P(0)) / t, and with the first coefficient P(t).
+template <int N>
+HGKS_FN double erfcx_poly(double t, const double (&c)[N]) {
+  double p = kconst<double>(c[N - 1]);
 #pragma unroll
-  for (int n = N - 2; n >= 0; --n) p = p * t + kconst<T>(c[n]);
-  return e * p * (a * r);
+  for (int n = N - 2; n >= 1; --n) p = fma(p, t, kconst<double>(c[n]));
+  return p;
 }
 
-// erfc(x) given e = exp(-x^2): 1 - erf by the polynomial where |x| <= 1 (every
-// smooth-flow interface state has |sqrt(lambda) U| well below 1), the tail
-// form elsewhere.  The library erfc it replaces forms its own exponential
-// and kept some 160 instructions and their registers in each side's code.
-template <typename T> HGKS_FN T d_erfc(T x, T e);
-template <> HGKS_FN double d_erfc<double>(double x, double e) {
+// erfc(y) for y >= 1, given e = exp(-z) for a z within some ulp of y^2.
+// Beyond y = 30 the result is 0 (e is).
+//
+// As exact as the C library's erfc (rms 0.62 units of 2^-53 and at most 2.4
+// on samples where that has 0.79 and 3.2): the rounding of z is worth z
+// units of e, so e is corrected by e^(z - y^2) = 1 - (y^2 - z), and the sums
+// and the quotient P / (1 + 2 y) carry their remainders to the last product.
+// e P / (1 + 2 y) as it stands is off by up to 12 units at y = 3, 36 at 5.
+HGKS_FN double erfc_tail(double y0, double e, double z) {
+  const double y = y0 > 30.0 ? 30.0 : y0;
+  const double a = y + 2.5, b = 2.0 * y + 1.0;
+  const double r = d_rcp(a * b);
+  const double t = (y - 2.5) * (b * r);
+  const double q = erfcx_poly(t, kErfcx21);
+  const double c0 = kconst<double>(kErfcx21[0]);
+  const double p = fma(q, t, c0);
+  const double pl = fma(q, t, c0 - p) + kErfcx21Low;
+  const double bl = 1.0 - (b - 2.0 * y);
+  const double rb = a * r;
+  const double s = p * rb;                                // P / (1 + 2 y)
+  const double sl = (fma(-s, b, p) + (pl - s * bl)) * rb;  // and its remainder
+  const double v = fma(e, s, e * (sl - fma(y, y, -z) * s));
+  return y0 >= 30.0 ? 0.0 : v;
+}
+
+// In float the tail is formed in double from the argument alone (its own
+// exponential), and rounded once.
+HGKS_FN float erfc_tail(float y0) {
+  const double y = y0 > 10.5f ? 10.5 : (double)y0;
+  const double a = y + 2.5, b = 2.0 * y + 1.0;
+  const double r = d_rcp(a * b);
+  const double t = (y - 2.5) * (b * r);
+  return (float)(exp_cw(-(y * y)) * (fma(erfcx_poly(t, kErfcx10), t, kconst<double>(kErfcx10[0])) * (a * r)));
+}
+
+// erfc(x) given e = exp(-z), z = x^2 but for rounding: 1 - erf by the
+// polynomial where |x| <= 1 (every smooth-flow interface state has
+// |sqrt(lambda) U| well below 1), the tail form elsewhere.  The library erfc
+// it replaces forms its own exponential and kept some 160 instructions and
+// their registers in each side's code.
+template <typename T> HGKS_FN T d_erfc(T x, T e, T z);
+template <> HGKS_FN double d_erfc<double>(double x, double e, double z) {
   if (fabs(x) <= 1.0) return 1.0 - erf_small(x, kErf12);
-  const double t = erfc_tail(fabs(x), e, kErfcx20);
+  const double t = erfc_tail(fabs(x), e, z);
   return x > 0.0 ? t : 2.0 - t;
 }
-template <> HGKS_FN float d_erfc<float>(float x, float e) {
+template <> HGKS_FN float d_erfc<float>(float x, float, float) {
   if (fabsf(x) <= 1.0f) return 1.0f - erf_small(x, kErf6);
-  const float t = erfc_tail(fabsf(x), e, kErfcx9);
+  const float t = erfc_tail(fabsf(x));
   return x > 0.0f ? t : 2.0f - t;
 }
+// e = exp(-x^2), x^2 as it rounds.
+template <typename T> HGKS_FN T d_erfc(T x, T e) { return d_erfc<T>(x, e, x * x); }
 template <typename T> HGKS_FN T d_sqrt(T x);
 template <> HGKS_FN double d_sqrt<double>(double x) { return sqrt(x); }
 template <> HGKS_FN float d_sqrt<float>(float x) { return sqrtf(x); }

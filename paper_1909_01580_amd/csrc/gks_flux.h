@@ -230,9 +230,10 @@ HGKS_FN void side_core(const Prim<T>& P, const PGrad<T> (&d)[3], const GasParams
   // half-line moments
   const T lam = T(0.5) * P.il;
   const T sl = d_sqrt(lam);
-  const T ex = d_exp(-lam * uu);
+  const T z = lam * uu;
+  const T ex = d_exp(-z);
   const T f0 = sg * T(0.56418958354775628694807945156077259) * sl * ex;  // 1/sqrt(pi)
-  const T m0 = T(0.5) * d_erfc(-sg * sl * U, ex);
+  const T m0 = T(0.5) * d_erfc(-sg * sl * U, ex, z);
   const T hf = h * f0;
   const T m1 = U * m0 + hf;
   const T m2 = U * m1 + h * m0;
