@@ -13,7 +13,7 @@ from paper_1909_01580_amd import hgks
 
 class Stream:
     def __init__(self, name, log):
-        self.name, self.log, self.cuda_stream = name, log, 0
+        self.name, self.log, self.cuda_stream, self.stream_id = name, log, 0, id(self)
 
     def wait_stream(self, other):
         self.log.append(("wait", self.name, other.name))
@@ -44,6 +44,7 @@ def world(monkeypatch):
     log = []
     own, caller = Stream("own", log), Stream("caller", log)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: caller)
+    monkeypatch.setattr(torch.accelerator, "current_stream", lambda device=None: caller)
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
     monkeypatch.setattr(torch, "empty", lambda *a, **k: Tensor("new", log))
     for name in hgks.EXPORTS:
