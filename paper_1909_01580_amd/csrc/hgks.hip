@@ -19,6 +19,7 @@
 #include "batch_kernels.h"
 #include "char_box.h"
 #include "char_hex.h"
+#include "result_slots.h"
 
 using namespace hgks;
 
@@ -165,7 +166,6 @@ struct hgks_ctx_s {
   char* ws;
   bool grid_set = false, state_set = false, next_set = false;
   hgks_status sticky = HGKS_OK;
-  double* host = nullptr;  // slot of pinned host memory for the results of the reductions
   double period[3];
   // Phase timing (hgks_profile_begin / hgks_profile_end).
   static constexpr int kProfCap = 512;
@@ -573,59 +573,47 @@ hgks_status set_box(hgks_ctx c, const double origin[3], const double length[3]) 
 }
 
 // Pinned host memory for the results of the reductions: one page per
-// process, allocated at the first reduction and kept, in slots of 8 doubles
-// that contexts take at their first reduction and give back when destroyed
-// (creating and destroying a context makes no device call, so both stay
-// possible while a stream is being captured).  A context that finds no slot
-// left, or no page, has its results copied from device scratch.
-constexpr int kResultSlots = 64;
-std::mutex g_result_mu;
-double* g_result_page = nullptr;
-bool g_result_tried = false;
-uint64_t g_result_free = ~0ull;
-
-double* result_slot() {
-  std::lock_guard<std::mutex> lock(g_result_mu);
-  if (!g_result_tried) {
-    g_result_tried = true;
-    if (hipHostMalloc((void**)&g_result_page, kResultSlots * 8 * sizeof(double), hipHostMallocPortable) !=
-        hipSuccess) {
-      g_result_page = nullptr;
-      (void)hipGetLastError();
-    }
+// process, allocated at the first reduction and kept.  (Creating and
+// destroying a context makes no device call, so both stay possible while a
+// stream is being captured; a reduction, which synchronises, never is.)
+double* result_page() {
+  void* p = nullptr;
+  if (hipHostMalloc(&p, 64 * 8 * sizeof(double), hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
   }
-  if (!g_result_page || !g_result_free) return nullptr;
-  const int k = __builtin_ctzll(g_result_free);
-  g_result_free &= g_result_free - 1;
-  return g_result_page + 8 * k;
+  return (double*)p;
 }
+ResultSlots<result_page> g_results;
+static_assert(decltype(g_results)::kCount * decltype(g_results)::kDoubles == 64 * 8, "one page");
 
-void result_slot_back(double* p) {
-  if (!p) return;
-  std::lock_guard<std::mutex> lock(g_result_mu);
-  g_result_free |= 1ull << ((p - g_result_page) / 8);
-}
+// The result of one call's reduction (at most 8 doubles): written by the
+// final kernel to a pinned slot, which the host reads after waiting for the
+// stream, or, with no slot free, to device scratch and copied.  From pinned
+// memory there is no copy to wait for: the 16^3 advection step, whose time
+// step is reduced between launches of a few microseconds, takes 66 us instead
+// of 81 with it and the shorter reductions.  A call that fails keeps its slot
+// for good: its kernel may still write there.
+class Result {
+ public:
+  explicit Result(hgks_ctx c) : c_(c), host_(g_results.take()) {}
+  double* out() const { return host_ ? host_ : c_->red() + c_->D.nred - 8; }
+  // Waits for the stream and gives the n results.
+  hgks_status fetch(int n, double* dst) {
+    if (!host_)
+      if (hgks_status s = check_hip(
+              c_, hipMemcpyAsync(dst, out(), n * sizeof(double), hipMemcpyDeviceToHost, c_->stream), "copy"))
+        return s;
+    if (hgks_status s = check_hip(c_, hipStreamSynchronize(c_->stream), "synchronise")) return s;
+    if (host_) std::memcpy(dst, host_, n * sizeof(double));
+    g_results.give(host_);
+    return HGKS_OK;
+  }
 
-// Where a reduction writes its result (at most 8 doubles).
-double* result(hgks_ctx c) {
-  if (!c->host) c->host = result_slot();
-  return c->host ? c->host : c->red() + c->D.nred - 8;
-}
-
-// Waits for the stream and gives the n results.  From pinned memory there is
-// no copy to wait for: the 16^3 advection step, whose time step is reduced
-// between launches of a few microseconds, takes 66 us instead of 81 with it and
-// the shorter reductions.
-hgks_status fetch_result(hgks_ctx c, int n, double* out) {
-  if (!c->host)
-    if (hgks_status s = check_hip(c, hipMemcpyAsync(out, c->red() + c->D.nred - 8, n * sizeof(double),
-                                                    hipMemcpyDeviceToHost, c->stream),
-                                  "copy"))
-      return s;
-  if (hgks_status s = check_hip(c, hipStreamSynchronize(c->stream), "synchronise")) return s;
-  if (c->host) std::memcpy(out, c->host, n * sizeof(double));
-  return HGKS_OK;
-}
+ private:
+  hgks_ctx c_;
+  double* host_;
+};
 
 }  // namespace
 
@@ -676,11 +664,9 @@ hgks_status hgks_create(const hgks_config* cfg, void* workspace_dev, size_t byte
 }
 
 hgks_status hgks_destroy(hgks_ctx ctx) {
-  if (ctx) {
+  if (ctx)
     for (int p = 0; p < HGKS_NPHASES; ++p)
       for (auto& e : ctx->prof_ev[p]) hipEventDestroy(e);
-    result_slot_back(ctx->host);
-  }
   delete ctx;
   return HGKS_OK;
 }
@@ -800,11 +786,12 @@ hgks_status hgks_max_dt(hgks_ctx c, double cfl, double* dt_host) {
   } else {
     hipLaunchKernelGGL(k_dt_box, dim3(nb), dim3(kBlock), 0, c->stream, c->q(), c->G, c->cfg.gamma, part, c->D.N);
   }
-  hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, result(c));
+  Result res(c);
+  hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, res.out());
   prof_mark(c, HGKS_PHASE_REDUCE, false);
   if (hgks_status s = launched(c, "max_dt")) return s;
   double m = 0.0;
-  if (hgks_status s = fetch_result(c, 1, &m)) return s;
+  if (hgks_status s = res.fetch(1, &m)) return s;
   if (!(m > 0.0)) return fail(HGKS_ENONPHYS, "non-physical state in max_dt");
   *dt_host = cfl * m;
   return HGKS_OK;
@@ -821,9 +808,10 @@ hgks_status hgks_totals(hgks_ctx c, double out[5]) {
     geo = c->geo();
   }
   hipLaunchKernelGGL(k_totals, dim3(nb), dim3(kBlock), 0, c->stream, c->q(), geo, c->G.vol, part, c->D.N, (int)nb);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, 5, result(c));
+  Result res(c);
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, 5, res.out());
   if (hgks_status s = launched(c, "totals")) return s;
-  return fetch_result(c, 5, out);
+  return res.fetch(5, out);
 }
 
 hgks_status hgks_check(hgks_ctx c, int64_t* nonphys, int64_t* fallback) {
@@ -835,10 +823,11 @@ hgks_status hgks_check(hgks_ctx c, int64_t* nonphys, int64_t* fallback) {
   // hexahedral one, so mask and cells coincide)
   hipLaunchKernelGGL(k_check_box, dim3(nb), dim3(kBlock), 0, c->stream, c->q(), c->mask(), c->G, c->cfg.gamma, part,
                      c->D.N, (int)nb);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, 2, result(c));
+  Result res(c);
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, 2, res.out());
   if (hgks_status s = launched(c, "check")) return s;
   double r[2];
-  if (hgks_status s = fetch_result(c, 2, r)) return s;
+  if (hgks_status s = res.fetch(2, r)) return s;
   *nonphys = (int64_t)r[0];
   *fallback = (int64_t)r[1];
   return HGKS_OK;
@@ -856,10 +845,11 @@ hgks_status hgks_kinetic_energy(hgks_ctx c, double rho0, double* ek_host) {
     geo = c->geo();
   }
   hipLaunchKernelGGL(k_kinetic, dim3(nb), dim3(kBlock), 0, c->stream, c->q(), geo, c->G.vol, part, c->D.N, (int)nb);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, 2, result(c));
+  Result res(c);
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kBlock), 0, c->stream, part, (int)nb, 2, res.out());
   if (hgks_status s = launched(c, "kinetic energy")) return s;
   double r[2];
-  if (hgks_status s = fetch_result(c, 2, r)) return s;
+  if (hgks_status s = res.fetch(2, r)) return s;
   *ek_host = r[0] / (rho0 * r[1]);
   return HGKS_OK;
 }
