@@ -290,7 +290,8 @@ hgks_status hgks_batch_max_dt(hgks_batch b, double cfl, double* dt_dev);
  * (its state is left as it was). */
 hgks_status hgks_batch_step(hgks_batch b, const double* dt_dev, int32_t n_stages);
 /* Workgroups of the persistent launch of a phase (hgks_phase; a multiple
- * of 8 between 8 and 65536; 0 restores one workgroup per tile). */
+ * of 8 between 8 and 65536; 0 restores one workgroup per tile), in units of
+ * 256 lanes: the flux launches four workgroups of one wave for each. */
 hgks_status hgks_batch_set_launch(hgks_batch b, int32_t phase, int32_t workgroups);
 /* Tile shapes of the batch (the autotuner's second dimension beside the
  * workgroup counts).  Cell tiles (reconstruction, fallback test, update,

@@ -163,9 +163,11 @@ __global__ void __launch_bounds__(kBlock) k_batch_char_recon(const BatchGrid<TC>
 // characteristic reconstruction.  The persistent FP64 form holds the walk's
 // values besides and takes a two-wave budget: at three it spills 36 bytes a
 // lane (PR: 184).  16 viscous and inviscid grids, ms per step at three
-// against two waves: 256 workgroups 11.45 and 10.74 (Pr 0.72: 12.68 and
-// 11.82), 512 7.64 and 6.40 (8.55 and 6.82), 8192 5.70 and 6.08 (6.63 and
-// 6.54); one workgroup per tile, 5.24 (5.44), is the default.
+// against two waves, by the workgroup count that the caller sets (in units
+// of 256 lanes, four of these one-wave workgroups each): 256 11.45 and 10.74
+// (Pr 0.72: 12.68 and 11.82), 512 7.64 and 6.40 (8.55 and 6.82), 8192 5.70
+// and 6.08 (6.63 and 6.54); one workgroup per tile, 5.24 (5.44), is the
+// default.
 template <typename TC, bool LOOP, bool PR = false, bool FS = false>
 __global__ void __launch_bounds__(kFluxLanes)
     __attribute__((amdgpu_waves_per_eu(sizeof(TC) == 8 && (FS || LOOP) ? 2 : 3)))

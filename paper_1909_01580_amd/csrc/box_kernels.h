@@ -42,8 +42,8 @@ struct BoxGrid {
   double wface[3];  // Gauss weight 1/4 times the face area, faces normal to d
   double vol;
   // Reciprocals for index splitting (split_index): extents n[0], n[1];
-  // nr[0], nr[1]; nf[d][0], nf[d][1].
-  double inv_n[2], inv_nr[2], inv_nf[3][2];
+  // nr[0], nr[1].
+  double inv_n[2], inv_nr[2];
   // Banded cell order of the flux blocks (face_cell): bands of `band`
   // rows along y; reciprocals of n0 band n2, n0 band and n0 (tail height).
   int band, band_full, band_tail;
@@ -95,7 +95,6 @@ inline void set_index_split(BoxGrid& G, int band = kFluxBand) {
   for (int a = 0; a < 2; ++a) {
     G.inv_n[a] = div_inv(G.n[a]);
     G.inv_nr[a] = div_inv(G.nr[a]);
-    for (int d = 0; d < 3; ++d) G.inv_nf[d][a] = div_inv(G.nf[d][a]);
   }
   G.band = G.n[1] < band ? G.n[1] : band;
   G.band_full = G.n[1] / G.band;
@@ -863,16 +862,9 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p) { p[threadIdx.x] = 0u; }
 
 // ---------------------------------------------------------------- flux
 // Local frame of a face normal to axis D: local axes (D, A, B) with
-// A = (D + 1) % 3 and B = (D + 2) % 3.  D is uniform over a workgroup, so
-// the plane offsets below are scalar arithmetic and one copy of the flux
-// code serves the three directions.
-struct FaceAxes {
-  int D, A, B;
-};
-
-HGKS_FN FaceAxes face_axes(int D) {
-  return FaceAxes{D, D == 2 ? 0 : D + 1, D == 0 ? 2 : D - 1};
-}
+// A = (D + 1) % 3 and B = (D + 2) % 3.  D is a template parameter (one copy
+// of the flux code per direction), so that every coefficient has a constant
+// offset from its cell's address.
 
 // Value and unit-cube gradient of a quadratic about the cell mean q at a
 // Gauss point of the face on the high (S = +1) or low (S = -1) side of local
@@ -1033,14 +1025,14 @@ template <int D, typename TC, bool PR = false, bool FS = false, bool DMA = false
 __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const uint32_t* __restrict__ mask,
                                               TC* __restrict__ face, const BoxGrid& G, const GasParams<TC>& gp,
                                               TC dt, TC idt, unsigned lb, unsigned sub, TC* stage = nullptr) {
-  const FaceAxes ax = face_axes(D);
+  constexpr int A = (D + 1) % 3, B = (D + 2) % 3;
   const int gpi = (int)(threadIdx.x & 3);
   const FaceLane fl = wave_face<D>(G, lb, sub * (kFluxLanes / 4), threadIdx.x >> 2);
   const unsigned iL = fl.iL;
   unsigned iR = fl.iR;
   const TC xa = (gpi >> 1) ? TC(kGaussNode) : TC(-kGaussNode);
   const TC xb = (gpi & 1) ? TC(kGaussNode) : TC(-kGaussNode);
-  const TC invd[3] = {TC(G.inv_dx[ax.D]), TC(G.inv_dx[ax.A]), TC(G.inv_dx[ax.B])};
+  const TC invd[3] = {TC(G.inv_dx[D]), TC(G.inv_dx[A]), TC(G.inv_dx[B])};
   auto mask_of = [&](unsigned i) { return *(const uint32_t*)((const char*)mask + i * 4u); };
   const bool fbL = (mask_of(iL) >> (4 * (2 * D + 1) + gpi)) & 1u;
   const bool fbR = (mask_of(iR) >> (4 * (2 * D) + gpi)) & 1u;
@@ -1165,7 +1157,7 @@ __device__ __forceinline__ void flux_box_face(const TC* __restrict__ coef, const
     // 32-bit byte offset from each row's uniform base
     const size_t NF = (size_t)G.nf[D][0] * G.nf[D][1] * G.nf[D][2];
     const unsigned fo = fl.f * (unsigned)sizeof(TC);
-    constexpr int gv[5] = {0, 1 + D, 1 + (D + 1) % 3, 1 + (D + 2) % 3, 4};
+    constexpr int gv[5] = {0, 1 + D, 1 + A, 1 + B, 4};
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
       *(TC*)((char*)(face + (size_t)gv[i] * NF) + fo) = F[i];

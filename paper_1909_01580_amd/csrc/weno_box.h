@@ -47,17 +47,10 @@ HGKS_FN constexpr int sidx3(const int (&o)[3]) { return sidx(o[0], o[1], o[2]); 
 template <typename T>
 struct BoxRecon {
   T c[9];      // combined quadratic
-  T bound;     // max over the 25 polynomials and the 24 Gauss points of
-               // |P_m(x_G) - Q_c| (a bound, see box_bound)
+  // Bound of |P_m(x_G) - Q_c| over the polynomials and the 24 face Gauss
+  // points: |xi_d| <= 1/2, |xi_d^2 - 1/12| <= 1/6, |xi_d xi_e| <= 1/(4 sqrt 3).
+  T bound;
 };
-
-// Bound of |P - Q_c| over the 24 face Gauss points for a polynomial with
-// linear coefficients l and (optional) quadratic coefficients: |xi_d| <= 1/2,
-// |xi_d^2 - 1/12| <= 1/6, |xi_d xi_e| <= 1/(4 sqrt 3).
-template <typename T>
-HGKS_FN T lin_bound(T bx, T by, T bz) {
-  return T(0.5) * (d_abs(bx) + d_abs(by) + d_abs(bz));
-}
 
 // Least-squares quadratic of the big stencil (closed form above).
 template <typename T>
