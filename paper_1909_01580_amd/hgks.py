@@ -256,21 +256,27 @@ def hgks_profile_end(h):
 
 
 # ------------------------------------------------------------ wrapper
-def _wait_for_caller(stream, device):
-    """Queues a wait of ``stream`` for the work on the caller's current
-    stream: a tensor that it reads may still be written there, and the memory
-    of a fresh one may still be in use there by the tensor that held it
-    before.  Returns the caller's stream, or None where no order is needed
-    (one stream) or possible (while the caller's stream is being captured
-    nothing queued on it runs, and a wait would draw ``stream`` into the
+def _caller(stream, device):
+    """The caller's current stream if work on ``stream`` has to be ordered with
+    it; None where it is the same one, or where it is being captured (nothing
+    queued on it runs then, and a wait would draw ``stream`` into the
     capture)."""
     # (a quarter of a microsecond; forming the stream's Python object takes two)
     if torch.accelerator.current_stream(device.index).stream_id == stream.stream_id:
         return None
     if torch.cuda.is_current_stream_capturing():
         return None
-    cur = torch.cuda.current_stream(device)
-    stream.wait_stream(cur)
+    return torch.cuda.current_stream(device)
+
+
+def _wait_for_caller(stream, device):
+    """Queues a wait of ``stream`` for the work on the caller's current
+    stream: a tensor that it reads may still be written there, and the memory
+    of a fresh one may still be in use there by the tensor that held it
+    before.  Returns the caller's stream, or None where there is no order."""
+    cur = _caller(stream, device)
+    if cur is not None:
+        stream.wait_stream(cur)
     return cur
 
 
@@ -547,7 +553,14 @@ class Batch:
 
     def get_state(self, i):
         out = torch.empty(self.shape(i), dtype=torch.float64, device=self.device)
-        _wait_for_caller(self.stream, self.device)
+        # The fresh memory's last tensor may still be in use on the caller's
+        # stream.  The call ends with the host waiting for the copy; waiting
+        # for the caller's stream here takes 16 us less than having the
+        # batch's stream wait for it (48 snapshots in a row: 45 against 61 us
+        # each).
+        cur = _caller(self.stream, self.device)
+        if cur is not None:
+            cur.synchronize()
         hgks_batch_get_state(self.h, i, out)
         hgks_batch_sync(self.h)
         return out

@@ -18,6 +18,9 @@ class Stream:
     def wait_stream(self, other):
         self.log.append(("wait", self.name, other.name))
 
+    def synchronize(self):
+        self.log.append(("host waits", self.name))
+
 
 class Tensor:
     """Stands for a device tensor of the caller's."""
@@ -63,11 +66,12 @@ CALLER_FIRST = ("wait", "own", "caller")
 
 
 def test_batch_get_state_waits_for_the_caller(world):
-    """The output's memory may have been dropped by the caller with work on it still queued."""
+    """The output's memory may have been dropped by the caller with work on
+    it still queued; the host, which waits for the copy, may do the waiting."""
     log, own, _ = world
     batch(own).get_state(0)
     copy = log.index(("call", "hgks_batch_get_state"))
-    assert CALLER_FIRST in log[:copy]
+    assert CALLER_FIRST in log[:copy] or ("host waits", "caller") in log[:copy]
     assert ("call", "hgks_batch_sync") in log[copy:]
 
 
@@ -107,7 +111,7 @@ def test_one_stream_needs_no_order(world):
     b.step(Tensor("dt", log))
     b.max_dt(0.35, Tensor("dt", log))
     b.get_state(0)
-    assert not [e for e in log if e[0] == "wait"]
+    assert not [e for e in log if e[0] in ("wait", "host waits")]
 
 
 def test_nothing_is_ordered_while_the_caller_is_captured(world, monkeypatch):
@@ -119,7 +123,7 @@ def test_nothing_is_ordered_while_the_caller_is_captured(world, monkeypatch):
     b.step(Tensor("dt", log))
     b.max_dt(0.35, Tensor("dt", log))
     b.get_state(0)
-    assert not [e for e in log if e[0] == "wait"]
+    assert not [e for e in log if e[0] in ("wait", "host waits")]
 
 
 def context(own):
