@@ -30,7 +30,7 @@ namespace hgks {
 // variable per wave), and the 24 sub-stencil fits (one per wave and round,
 // four rounds; every wave then projects the round's six).  One lane per cell
 // repeated the 24 fits for every face, 48,600 vector instructions per cell
-// in one serial chain at two waves per SIMD; here a lane runs 6,800, six of
+// in one serial chain at two waves per SIMD; here a lane runs 6,930, six of
 // them per cell, at three waves per SIMD: 463 -> 254 us per launch on
 // 56x41x36 cells (mixed).  Twelve waves fill a compute unit evenly; of
 // workgroups of six only one fitted (310 us).

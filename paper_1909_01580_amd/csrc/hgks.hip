@@ -275,9 +275,9 @@ TC* face_coef(hgks_ctx c) {
 // Cells of the reconstruction box up to which the reconstruction splits a
 // cell's variables over waves: up to about 40,000 cells the five waves per
 // 64 cells are resident at once (three per SIMD).  One launch, split against
-// one lane per cell, FP64: 16^3 6.8 against 13.9 us, 33x20x17 7 against
-// 14.7 us, but 42^3 (two rounds of waves either way, and each wave finds its
-// neighbours itself) 25 against 21.5 us.
+// one lane per cell, FP64: 16^3 7.1 against 12.9 us, 33x20x17 8.7 against
+// 14.1 us, but 42^3 (two rounds of waves either way, and each wave finds its
+// neighbours itself) 26.6 against 22.0 us.
 constexpr size_t kSplitMax = 40000;
 
 // Empties the list of flagged cells: before the first stage, and after a

@@ -166,7 +166,9 @@ HGKS_FN void weno_box(const T (&d)[27], const WenoParams<T>& P, BoxRecon<T>& out
       tsum += d_abs(beta0 - b0);
       tsum += d_abs(beta0 - b1);
       // One reciprocal each: the product of two indicators, whose reciprocal
-      // would serve both, leaves the format for a small epsilon or large data.
+      // would serve both (128^3 FP64 0.31 instead of 0.32 ms a launch),
+      // leaves the format for a small epsilon or large data, and a check of
+      // its range keeps the operands alive (256 registers instead of 154).
       const T rp1 = d_rcp(b0 + P.eps), rm1 = d_rcp(b1 + P.eps);
       rp += rp1;
       rm += rm1;
